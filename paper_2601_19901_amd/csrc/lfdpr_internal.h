@@ -115,6 +115,7 @@ struct SplatArgs {
   int32_t q_rows, q_views, q_bands, q_subsets;  // tile: q_rows rows x q_views views x W
   int32_t q_bands_item;        // bands per item (q_bands over all items)
   int32_t q_block;             // threads per quilt workgroup: 1024, or 512 (two tiles per CU)
+  int32_t q_queue;             // 1: the tile's LDS also holds its waves' covered-pixel queues
   uint32_t* out_rgba;          // the views, [view][y][x]
   float* out_depth;            // optional, [view][y][x]
 };
@@ -169,6 +170,8 @@ void launch_splat(const SplatArgs& a, int grid_blocks, hipStream_t s);
 // the quilt: band lists (bins), then one workgroup per (band, view subset)
 // tile in decreasing band size; the tile's LDS bytes
 size_t quilt_lds_bytes(int32_t rows, int32_t views, int32_t W, int32_t H);
+// LDS of the covered-pixel queues of a tile workgroup, beyond quilt_lds_bytes
+size_t quilt_queue_bytes(int32_t block);
 constexpr int kQuiltBandCap = 8192;  // bands of a frame or batch frame
 // Lets the tile kernels take up to lds bytes of LDS (once per device, before
 // any launch or graph capture).

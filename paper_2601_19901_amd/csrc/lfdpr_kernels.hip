@@ -12,9 +12,9 @@
 //                 mip fetches (tv_min, tv_max)                (Sec. 3.3); for
 //                 the triangle-view order and the quilt also the point's
 //                 splat rectangle (and, for the quilt, its pixel rows)
-//   k_splat       one lane per point, looping over the views: splat box,
-//                 inside-triangle test, cell ownership, Eqs. 8-9, 64-bit
-//                 atomicMin of (depth, colour)                (Sec. 3.2, 3.3, 5.1)
+//   k_splat       a wave takes 64 points through the views: splat boxes, then
+//                 their covered pixels 64 at a time: cell ownership, Eqs. 8-9,
+//                 64-bit atomicMin of (depth, colour)         (Sec. 3.2, 3.3, 5.1)
 //   k_qcount, k_qplan, k_qscatter   the quilt's band lists: points binned by
 //                 the pixel rows their splat reaches           (Sec. 3.2)
 //   k_splat_quilt one workgroup per tile (a band of rows x a subset of the
@@ -644,13 +644,6 @@ __global__ void __launch_bounds__(256) k_fetch(EmitArgs a) {
 
 // ------------------------------------------------------------------ a3: splat
 
-// One lane per point, looping over the views.  Everything that does not depend
-// on the eye offset b is computed once per point: the cell's corner projections
-// (x = A - b*C is affine in b), the row range, the cell-centre depth.  Pixel
-// ray slopes (x+0.5-cx)/fx and (y+0.5-cy)/fy come from per-block LDS tables
-// holding exactly the values the inline expressions give.  The integer edge
-// functions are evaluated in double, which represents every value exactly
-// (|E| < 2^50), and stepped along x.
 // An item table entry read by all active lanes of a wave from one address,
 // moved to scalar registers word by word.
 __device__ __forceinline__ Item load_uniform(const Item* p) {
@@ -696,38 +689,114 @@ __device__ __forceinline__ float uniform_f32(float x) {
   return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
 }
 
-// One point against every view of its item's rig; `item` is wave-uniform.
-// kPBR: the colour is shaded (material record tm[tri], point words pm).
+// Orders this wave's LDS accesses around it (its lanes exchange data there).
+__device__ __forceinline__ void wave_sync_lds() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// A wave's 64 points (one per lane) against views [r_begin, r_end) of their
+// item's rig; `item` and the view range are wave-uniform, every lane of the
+// wave calls, and lanes with `valid` false take part without a point.
+//
+// What bounds it: vector issue.  A (point, view) pair's splat box holds 1.7
+// pixels on average but up to 4.4 in the slowest lane of 64, and of the box
+// pixels 54 % lie inside the triangle and 29 % belong to the point, so a lane
+// that carries its own pixels through the ray, the division, the ownership
+// test, the colour and the key idles most of the time.  Three passes instead:
+//   box pixels      per lane: 32-bit edge functions stepped over the box (the
+//                   one part that walks at the pace of the largest box);
+//   covered pixels  queued in LDS and taken 64 at a time, whichever lanes and
+//                   views they came from: ray, depth, ownership, colour, key.
+//                   The point's data come from its lane's registers
+//                   (ds_bpermute), the view's from lanes that hold the tables;
+//   owned pixels    (kPBR) queued once more, so that shading -- four fifths of
+//                   the instructions there -- runs on full waves.
+// A box of more than kLaneBox pixels would hold its whole wave (one lane of a
+// grazing triangle took 1.5 ms): all lanes walk it, 64 pixels at a time.
+// Measured on a million-triangle frame (3.0M points, 48 views of 512 x 512)
+// against one lane carrying each pixel to its key: 8.3e8 -> 4.8e8 vector
+// instructions, 2.48 -> 1.17 ms.
+// A queue entry is one word: lane (6 bits), x, y, and the view within a group
+// of as many views as the remaining bits number (64 at most; 4 at 4096 x 4096).
+//
+// Edge functions: the triangle's vertices are taken in the order that makes
+// its area positive for an eye in front of it, so dy, the tie rule (an edge
+// owns its ties iff dy > 0, or dy == 0 and the third vertex lies below it) and
+// the distance of the first row from each vertex do not depend on the view.
+// With spans up to kSmallSpan (124 pixels) every term fits 32 bits and every
+// factor 24.  A larger triangle, or one whose snapped area is not positive in
+// this view, is walked by the whole wave with the exact 64-bit test
+// (covered_wide).
+//
 // kQuilt: only the views and rows of tile *qt, keys in its LDS; the splat
 // rectangle's corners, rows and cell-centre depth come from the point's
-// PointBox (the same values, computed at emission).
-template <bool kPBR, bool kQuilt = false>
-__device__ __forceinline__ void splat_point(const Item& item, const Point& pt, const TriRec& T, uint32_t flags,
-                                            int32_t i, int32_t j, const float* tx, const float* ty,
-                                            const SplatArgs& a, uint64_t p, uint32_t& written,
-                                            const QuiltTile* qt = nullptr) {
-  const int64_t vpx = (int64_t)item.rig.W * item.rig.H;
-  const int32_t H8 = 256 * item.rig.H, W8 = 256 * item.rig.W;
+// PointBox (the same values, computed at emission).  queue == nullptr (a tile
+// that leaves no LDS for it): each lane takes its own covered pixel at once.
+constexpr int kSplatQueue = 128;        // entries: 63 waiting and 64 new ones at most
+constexpr int32_t kLaneBox = 16;        // pixels of a box that its lane walks alone
+constexpr float kRound = 12582912.0f;    // 1.5 * 2^23: adding it rounds to an integer (ties to even) ...
+constexpr int32_t kRoundBits = 0x4B400000;  // ... held in the sum's bits, offset by this
+constexpr float kGuardQ8 = kGuard * 256.0f;
+constexpr int32_t kSmallSpan = 31744;   // Q8: |E| <= 2 * 31744^2 + one step < 2^31
+
+// a * b + c with 24-bit factors
+__device__ __forceinline__ int32_t mad24(int32_t a, int32_t b, int32_t c) {
+  int32_t d;
+  asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+  return d;
+}
+
+__device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
+__device__ __forceinline__ float from_lane(int src4, float v) {
+  return __int_as_float(__builtin_amdgcn_ds_bpermute(src4, __float_as_int(v)));
+}
+__device__ __forceinline__ uint32_t from_lane(int src4, uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_ds_bpermute(src4, (int)v);
+}
+
+// Is the centre of pixel (x, y) inside the Q8 triangle?  Exact for every
+// vertex of the guard band.
+__device__ __forceinline__ bool covered_wide(int32_t x, int32_t y, const int32_t qx[3], const int32_t qy[3]) {
+  const int64_t a2 = (int64_t)(qx[1] - qx[0]) * (qy[2] - qy[0]) - (int64_t)(qy[1] - qy[0]) * (qx[2] - qx[0]);
+  if (a2 == 0) return false;
+  const int32_t px = 256 * x + 128, py = 256 * y + 128, s = a2 < 0 ? -1 : 1;
+  bool in = true;
+#pragma unroll
+  for (int e = 0; e < 3; ++e) {
+    const int eb = e == 2 ? 0 : e + 1;
+    const int32_t dx = s * (qx[eb] - qx[e]), dy = s * (qy[eb] - qy[e]);
+    const int64_t E = (int64_t)dx * (py - qy[e]) - (int64_t)dy * (px - qx[e]);
+    in = in && (E > 0 || (E == 0 && (dy > 0 || (dy == 0 && dx > 0))));
+  }
+  return in;
+}
+
+template <bool kPBR, bool kQuilt>
+__device__ __forceinline__ void splat_wave(const Item& item, bool valid, uint64_t p, const Point& pt, const TriRec& T,
+                                           const float* tx, const float* ty, const SplatArgs& a, uint32_t* queue,
+                                           uint2* own_queue, int r_begin, int r_end, uint32_t& written,
+                                           const QuiltTile* qt = nullptr) {
   const Rig& rg = item.rig;
-  uint64_t* const keys = item.keys;
-  const bool rowmajor = item.key_layout != 0;
-  const int64_t row_stride = rowmajor ? (int64_t)rg.n_views * rg.W : rg.W;
+  const int lane = threadIdx.x & 63;
+  const int32_t i = (int16_t)(pt.ij & 0xFFFFu), j = (int16_t)(pt.ij >> 16);
+  const int32_t H8 = 256 * rg.H;
   // view-independent vertex rows (guard band on y) and triangle row range
-  if (!(fabsf(T.y0) < kGuard) || !(fabsf(T.y1) < kGuard) || !(fabsf(T.y2) < kGuard)) return;
-  const int32_t qy0 = (int32_t)rintf(T.y0 * 256.0f), qy1 = (int32_t)rintf(T.y1 * 256.0f),
-                qy2 = (int32_t)rintf(T.y2 * 256.0f);
-  if ((qy0 < 0 && qy1 < 0 && qy2 < 0) || (qy0 > H8 && qy1 > H8 && qy2 > H8)) return;
-  const int32_t ymin = min(qy0, min(qy1, qy2)), ymax = max(qy0, max(qy1, qy2));
-  const int32_t Y0 = max(0, -((128 - ymin) >> 8));
-  const int32_t Y1 = min(rg.H - 1, (ymax - 128) >> 8);
-  if (Y0 > Y1) return;
+  bool alive = valid && fabsf(T.y0) < kGuard && fabsf(T.y1) < kGuard && fabsf(T.y2) < kGuard;
+  const int32_t qy[3] = {(int32_t)rintf(T.y0 * 256.0f), (int32_t)rintf(T.y2 * 256.0f), (int32_t)rintf(T.y1 * 256.0f)};
+  const int32_t ymin = min(qy[0], min(qy[1], qy[2])), ymax = max(qy[0], max(qy[1], qy[2]));
+  alive = alive && ymax >= 0 && ymin <= H8;
+  int32_t by0 = max(0, (ymin + 127) >> 8), by1 = min(rg.H - 1, (ymax - 128) >> 8);
   // splat box corners (row-end extended cell), projected except for the eye offset
   float cA[4], cC[4];
   bool full;
-  int32_t by0 = Y0, by1 = Y1;
   if constexpr (kQuilt) {
     // the stored rows are clamped to [-1, H], which leaves their intersection
-    // with [Y0, Y1] (inside [0, H-1]) unchanged or empty as before
+    // with the triangle's rows (inside [0, H-1]) unchanged or empty as before
     const PointBox& B = *qt->box;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -743,164 +812,328 @@ __device__ __forceinline__ void splat_point(const Item& item, const Point& pt, c
     by1 = min(by1, qt->y_hi);
   } else {
     float ymn, ymx;
-    splat_corners(rg, T, i, j, flags, cA, cC, ymn, ymx, full);
+    splat_corners(rg, T, i, j, pt.tri_flags >> 28, cA, cC, ymn, ymx, full);
     if (!full) {
-      int32_t r0 = (int32_t)ceilf(clamp_big(ymn - 0.515625f)), r1 = (int32_t)floorf(clamp_big(ymx - 0.484375f));
-      by0 = max(r0, by0);
-      by1 = min(r1, by1);
+      by0 = max((int32_t)ceilf(clamp_big(ymn - 0.515625f)), by0);
+      by1 = min((int32_t)floorf(clamp_big(ymx - 0.484375f)), by1);
     }
   }
-  if (by0 > by1) return;
-  // cell-centre terms of Eqs. 8-9 and the ownership bounds
-  float cs = 0.0f, ct = 0.0f, Zc = 0.0f, Zc3;
-  if (kQuilt && !kPBR) {
-    Zc3 = qt->box->zc3;
-  } else {
-    cs = (float)i / T.sx;
-    ct = (float)j / T.sy;
-    Zc = (T.p0z + cs * T.uz) + ct * T.wz;
-    Zc3 = (Zc * Zc) * Zc;
-  }
-  F3 pc{0.0f, 0.0f, Zc}, Tf{0.0f, 0.0f, 0.0f}, Bf{0.0f, 0.0f, 0.0f};
-  uint4 pm{0u, 0u, 0u, 0u};
-  if constexpr (kPBR) {
-    // cell centre in camera space, tangent frame, material bytes of the point
-    pc.x = (T.p0x + cs * T.ux) + ct * T.wx;
-    pc.y = (T.p0y + cs * T.uy) + ct * T.wy;
-    const TriMat& M = a.tm[pt.tri_flags & 0x0FFFFFFFu];
-    Tf = F3{M.tx, M.ty, M.tz};
-    Bf = F3{M.bx, M.by, M.bz};
-    pm = a.pmat[p];
-  }
-  const float Acell = 1.0f / (T.sx * T.sy);
-  const float suv = Acell * T.ruv;
-  const float fi0 = (float)i, fi1 = (float)(i + 1), fj0 = (float)j, fj1 = (float)(j + 1);
-  const bool oilo = flags & F_ILO, oihi = flags & F_IHI, ojlo = flags & F_JLO, ojhi = flags & F_JHI;
-  const uint32_t lo02 = pt.tvmin & 0x00FF00FFu, lo13 = (pt.tvmin >> 8) & 0x00FF00FFu;
-  const uint32_t hi02 = pt.tvmax & 0x00FF00FFu, hi13 = (pt.tvmax >> 8) & 0x00FF00FFu;
-  const float p0y2 = T.p0y * T.p0y, p0z2 = T.p0z * T.p0z;
-  const int r_begin = kQuilt ? qt->r_lo : 0, r_end = kQuilt ? qt->r_hi : rg.n_views;
-  float b_next = table_f32(rg.eye, r_begin);  // the next view's eye offset, one iteration ahead
-  for (int r = r_begin; r < r_end; ++r) {
-    const float b = b_next;
-    if (r + 1 < r_end) b_next = table_f32(rg.eye, r + 1);
-    const float delta = T.h - T.nx * b;
-    if (!faces_eye(T.p0x, p0y2, p0z2, delta, b)) continue;
-    // splat box columns first: empty for about a third of the (point, view) pairs
-    int32_t cbx0 = 0, cbx1 = rg.W - 1;
-    if (!full) {
-      float xmn = cA[0] - b * cC[0], xmx = xmn;
+  if (full) {  // no box limit: columns -2^29 .. 2^29 in every view
 #pragma unroll
-      for (int k = 1; k < 4; ++k) {
-        float xx = cA[k] - b * cC[k];
-        xmn = xx < xmn ? xx : xmn;
-        xmx = xx > xmx ? xx : xmx;
-      }
-      cbx0 = max(cbx0, (int32_t)ceilf(clamp_big(xmn - 0.515625f)));
-      cbx1 = min(cbx1, (int32_t)floorf(clamp_big(xmx - 0.484375f)));
-      if (cbx0 > cbx1) continue;
+    for (int k = 0; k < 4; ++k) {
+      cA[k] = (k & 1) ? 0x1p29f : -0x1p29f;
+      cC[k] = 0.0f;
     }
-    const float x0 = T.a0 - b * T.c0, x1 = T.a1 - b * T.c1, x2 = T.a2 - b * T.c2;
-    if (!(fabsf(x0) < kGuard) || !(fabsf(x1) < kGuard) || !(fabsf(x2) < kGuard)) continue;
-    int32_t qx[3] = {(int32_t)rintf(x0 * 256.0f), (int32_t)rintf(x1 * 256.0f), (int32_t)rintf(x2 * 256.0f)};
-    int32_t qy[3] = {qy0, qy1, qy2};
-    if ((qx[0] < 0 && qx[1] < 0 && qx[2] < 0) || (qx[0] > W8 && qx[1] > W8 && qx[2] > W8)) continue;
-    const double a2 = (double)(qx[1] - qx[0]) * (double)(qy[2] - qy[0]) -
-                      (double)(qy[1] - qy[0]) * (double)(qx[2] - qx[0]);
-    if (a2 == 0.0) continue;
-    if (a2 < 0.0) {
-      int32_t u = qx[1]; qx[1] = qx[2]; qx[2] = u;
-      u = qy[1]; qy[1] = qy[2]; qy[2] = u;
+  }
+  alive = alive && by0 <= by1;
+  if (!__builtin_amdgcn_ballot_w64(alive)) return;
+  // cell-centre terms of Eqs. 8-9
+  float pcx = 0.0f, pcy = 0.0f, zc;  // zc: the centre's depth (kPBR) or its cube
+  if (kQuilt && !kPBR) {
+    zc = qt->box->zc3;
+  } else {
+    const float cs = (float)i / T.sx, ct = (float)j / T.sy;
+    zc = (T.p0z + cs * T.uz) + ct * T.wz;
+    if constexpr (kPBR) {
+      pcx = (T.p0x + cs * T.ux) + ct * T.wx;
+      pcy = (T.p0y + cs * T.uy) + ct * T.wy;
+    } else {
+      zc = (zc * zc) * zc;
     }
-    const int32_t xmin = min(qx[0], min(qx[1], qx[2])), xmax = max(qx[0], max(qx[1], qx[2]));
-    const int32_t bx0 = max(cbx0, -((128 - xmin) >> 8));
-    const int32_t bx1 = min(cbx1, (xmax - 128) >> 8);
-    const int32_t ry0 = kQuilt ? by0 : (full ? Y0 : by0), ry1 = kQuilt ? by1 : (full ? Y1 : by1);
-    if (bx0 > bx1 || ry0 > ry1) continue;
-    // colour of this point in this view (Eqs. 8-9)
+  }
+  const float acell = 1.0f / (T.sx * T.sy);
+  const float p0y2 = T.p0y * T.p0y, p0z2 = T.p0z * T.p0z;
+  // lattice cell of the point; a NaN bound (an end of its row or lattice) excludes nothing
+  const uint32_t flags = pt.tri_flags >> 28;
+  const float kNone = __uint_as_float(0x7FC00000u);
+  const float s_lo = (flags & F_ILO) ? kNone : (float)i, s_hi = (flags & F_IHI) ? kNone : (float)(i + 1);
+  const float t_lo = (flags & F_JLO) ? kNone : (float)j, t_hi = (flags & F_JHI) ? kNone : (float)(j + 1);
+  // edges 0-1, 1-2, 2-0 of the vertices 0, 2, 1 of the record; in 1/256 px (an exact scaling)
+  const float va[3] = {T.a0 * 256.0f, T.a2 * 256.0f, T.a1 * 256.0f};
+  const float vc[3] = {T.c0 * 256.0f, T.c2 * 256.0f, T.c1 * 256.0f};
+  int32_t ndy[3], py[3], tie[3];
+#pragma unroll
+  for (int e = 0; e < 3; ++e) {
+    const int eb = e == 2 ? 0 : e + 1, ec = eb == 2 ? 0 : eb + 1;
+    ndy[e] = qy[e] - qy[eb];
+    py[e] = 256 * by0 + 128 - qy[e];
+    tie[e] = (ndy[e] < 0 || (ndy[e] == 0 && qy[ec] > qy[e])) ? 0 : -1;
+  }
+  const uint64_t tall_m = __builtin_amdgcn_ballot_w64(ymax - ymin > kSmallSpan);
+  const float x_last = (float)(rg.W - 1);
+  const int32_t tsum = tie[0] + tie[1] + tie[2];
+  // Facing and guard-band tests that hold for every eye are settled once: the
+  // plane distance, its square, the eye distance and each projected x are
+  // monotone in the eye offset (rounding keeps order), so both ends decide.
+  bool safe;
+  {
+    const float d0 = T.h - T.nx * rg.eye_lo, d1 = T.h - T.nx * rg.eye_hi;
+    const float dm = fminf(fabsf(d0), fabsf(d1));
+    const float e0 = T.p0x - rg.eye_lo, e1 = T.p0x - rg.eye_hi;
+    const float d2 = fmaxf((e0 * e0 + p0y2) + p0z2, (e1 * e1 + p0y2) + p0z2);
+    safe = d0 < 0.0f && d1 < 0.0f && dm * dm >= d2 * 0x1p-16f;
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      safe = safe && fabsf(va[k] - rg.eye_lo * vc[k]) < kGuardQ8 && fabsf(va[k] - rg.eye_hi * vc[k]) < kGuardQ8;
+  }
+  const uint64_t alive_m = __builtin_amdgcn_ballot_w64(alive);
+  const bool all_safe = (alive_m & ~__builtin_amdgcn_ballot_w64(safe)) == 0;
+  const int32_t nrows = by1 - by0 + 1;
+  // queue entries: lane | x << 6 | y << ysh | view of the group << rsh
+  const int xb = rg.W > 1 ? 32 - __builtin_clz((uint32_t)rg.W - 1u) : 0, yb = rg.H > 1 ? 32 - __builtin_clz((uint32_t)rg.H - 1u) : 0;
+  const int ysh = 6 + xb, rsh = 6 + xb + yb;
+  const uint32_t xm = (1u << xb) - 1u, ym = (1u << yb) - 1u;
+  const int group = rsh <= 26 ? 64 : 1 << (32 - rsh);
+  const bool rowmajor = item.key_layout != 0;
+  uint32_t qn = 0, on_n = 0;  // waiting entries: covered pixels; owned pixels (kPBR)
+  float eye_l = 0.0f, ks_l = 0.0f;  // eye offset and lens shift of view g0 + lane
+  int g0 = r_begin;
+
+  // Colour (Eqs. 8-9; kPBR: shaded) of owned pixel e at depth Z, and its key.
+  auto emit_key = [&](uint32_t e, float Z, bool on, float b, float nx, float delta) {
+    const int src = (int)((e & 63u) << 2);
+    const uint32_t x = (e >> 6) & xm, y = (e >> ysh) & ym, rr = e >> rsh;
+    const float ac = from_lane(src, acell), ruv = from_lane(src, T.ruv);
+    const float smin = from_lane(src, T.smin), smax = from_lane(src, T.smax), irange = from_lane(src, T.irange);
+    const uint32_t lo = from_lane(src, pt.tvmin), hi = from_lane(src, pt.tvmax);
+    float zc3 = from_lane(src, zc);
+    F3 ng{nx, 0.0f, 0.0f}, pc{0.0f, 0.0f, zc3};
+    uint32_t tri = 0;
+    uint64_t pp = 0;
+    if constexpr (kPBR) {
+      ng.y = from_lane(src, T.ny);
+      ng.z = from_lane(src, T.nz);
+      pc.x = from_lane(src, pcx);
+      pc.y = from_lane(src, pcy);
+      zc3 = (zc3 * zc3) * zc3;
+      tri = from_lane(src, pt.tri_flags) & 0x0FFFFFFFu;
+      pp = (uint64_t)from_lane(src, (uint32_t)p) | ((uint64_t)from_lane(src, (uint32_t)(p >> 32)) << 32);
+    }
+    if (!on) return;
     const float ad = fabsf(delta);
-    const float Ar = Zc3 / (rg.fxfy * ad);
-    const float vse = Acell < Ar ? T.ruv * Ar : suv;
-    const float vs = vse < T.smin ? T.smin : (vse > T.smax ? T.smax : vse);
-    const float tau = (vs - T.smin) * T.irange;
+    const float Ar = zc3 / (rg.fxfy * ad);
+    const float vse = ac < Ar ? ruv * Ar : ac * ruv;
+    const float vs = vse < smin ? smin : (vse > smax ? smax : vse);
+    const float tau = (vs - smin) * irange;
     int32_t tq = (int32_t)floorf(tau * 256.0f + 0.5f);
     tq = tq < 0 ? 0 : (tq > 256 ? 256 : tq);
     const uint32_t wa = (uint32_t)(256 - tq), wz = (uint32_t)tq;
-    uint32_t col = (((lo02 * wa + hi02 * wz + 0x00800080u) >> 8) & 0x00FF00FFu) |
-                   ((((lo13 * wa + hi13 * wz + 0x00800080u) >> 8) & 0x00FF00FFu) << 8);
+    auto lerp_even = [&](uint32_t u, uint32_t v) {  // bytes 0 and 2 of each word
+      return (((u & 0x00FF00FFu) * wa + (v & 0x00FF00FFu) * wz + 0x00800080u) >> 8) & 0x00FF00FFu;
+    };
+    uint32_t col = lerp_even(lo, hi) | (lerp_even(lo >> 8, hi >> 8) << 8);
     if constexpr (kPBR) {
       // the normal map and the roughness / metallic bytes take the same tau
-      auto lerp_even = [&](uint32_t lo, uint32_t hi) {  // bytes 0 and 2 of each word
-        return (((lo & 0x00FF00FFu) * wa + (hi & 0x00FF00FFu) * wz + 0x00800080u) >> 8) & 0x00FF00FFu;
-      };
+      const TriMat& M = a.tm[tri];
+      const uint4 pm = a.pmat[pp];
       const uint32_t nrm = lerp_even(pm.x, pm.y) | (lerp_even(pm.x >> 8, pm.y >> 8) << 8);
       const uint32_t rq = ((pm.z & 255u) * wa + ((pm.z >> 8) & 255u) * wz + 128u) >> 8;
       const uint32_t mq = (((pm.z >> 16) & 255u) * wa + (pm.z >> 24) * wz + 128u) >> 8;
-      col = shade_splat(a.sh, F3{T.nx, T.ny, T.nz}, Tf, Bf, pc, b, col, nrm, rq, mq);
+      col = shade_splat(a.sh, ng, F3{M.tx, M.ty, M.tz}, F3{M.bx, M.by, M.bz}, pc, b, col, nrm, rq, mq);
     }
-    const float ks = table_f32(rg.kshift, r);
-    const float cu = T.ux * (b - T.p0x) - T.cu0;
-    const float cw = T.wx * (b - T.p0x) - T.cw0;
-    // edge functions with the tie rule folded in as +0.5 (E integer: E+0.5 > 0 <=> E >= 0)
-    double edx[3], edy[3], bias[3];
-#pragma unroll
-    for (int e = 0; e < 3; ++e) {
-      const int eb = e == 2 ? 0 : e + 1;
-      const int32_t dx = qx[eb] - qx[e], dy = qy[eb] - qy[e];
-      edx[e] = (double)dx;
-      edy[e] = (double)dy;
-      bias[e] = (dy > 0 || (dy == 0 && dx > 0)) ? 0.5 : 0.0;
+    const uint64_t key = ((uint64_t)__float_as_uint(Z) << 32) | col;
+    if constexpr (kQuilt) {
+      lds_key_min(qt->keys + (((g0 - qt->r_lo + (int)rr) * qt->rows + ((int)y - qt->y_lo)) * rg.W + (int)x), key);
+    } else {
+      const uint32_t r = (uint32_t)g0 + rr;
+      const uint32_t row = rowmajor ? y * (uint32_t)rg.n_views + r : r * (uint32_t)rg.H + y;
+      key_min(item.keys + ((uint64_t)row * (uint32_t)rg.W + x), key);
     }
-    uint64_t* kv = keys + (rowmajor ? (int64_t)r * rg.W : (int64_t)r * vpx);
-    const int32_t kq = kQuilt ? ((r - qt->r_lo) * qt->rows - qt->y_lo) * rg.W : 0;  // tile key of (y, x): kq + y*W + x
-    const int32_t pxq0 = 256 * bx0 + 128, pyq0 = 256 * ry0 + 128;
-    // edge functions at (bx0, ry0), stepped by whole pixels (all values are
-    // integers + 0.5 below 2^51, so every step is exact)
-    double R0 = edx[0] * (double)(pyq0 - qy[0]) - edy[0] * (double)(pxq0 - qx[0]) + bias[0];
-    double R1 = edx[1] * (double)(pyq0 - qy[1]) - edy[1] * (double)(pxq0 - qx[1]) + bias[1];
-    double R2 = edx[2] * (double)(pyq0 - qy[2]) - edy[2] * (double)(pxq0 - qx[2]) + bias[2];
-    const double st0 = edy[0] * 256.0, st1 = edy[1] * 256.0, st2 = edy[2] * 256.0;
-    const double sr0 = edx[0] * 256.0, sr1 = edx[1] * 256.0, sr2 = edx[2] * 256.0;
-    for (int32_t y = ry0; y <= ry1; ++y, R0 += sr0, R1 += sr1, R2 += sr2) {
-      double E0 = R0, E1 = R1, E2 = R2;
-      const float ry = ty[y];
-      const float nyr = T.ny * ry, uyr = T.uy * ry, wyr = T.wy * ry;
-      for (int32_t x = bx0; x <= bx1; ++x) {
-        const bool in = E0 > 0.0 && E1 > 0.0 && E2 > 0.0;
-        E0 -= st0;
-        E1 -= st1;
-        E2 -= st2;
-        if (!in) continue;
-        const float rx = tx[x] - ks;
-        const float den = (T.nx * rx + nyr) + T.nz;
-        const float Z = delta / den;
-        if (!(Z > 0.0f) || isinf(Z)) continue;
-        const float ur = (T.ux * rx + uyr) + T.uz;
-        const float wr = (T.wx * rx + wyr) + T.wz;
-        const float sv = T.sx * (Z * ur + cu) + 0.5f;
-        const float tv = T.sy * (Z * wr + cw) + 0.5f;
-        const bool own = (oilo || sv >= fi0) && (oihi || sv < fi1) && (ojlo || tv >= fj0) && (ojhi || tv < fj1);
-        if (own) {
-          if constexpr (kQuilt)
-            lds_key_min(qt->keys + (kq + y * rg.W + x), ((uint64_t)__float_as_uint(Z) << 32) | col);
-          else
-            key_min(&kv[(int64_t)y * row_stride + x], ((uint64_t)__float_as_uint(Z) << 32) | col);
-          ++written;
+  };
+
+  auto emit_queued = [&](uint2 q, bool on) {
+    const float b = from_lane((int)((q.x >> rsh) << 2), eye_l), nx = from_lane((int)((q.x & 63u) << 2), T.nx);
+    emit_key(q.x, __uint_as_float(q.y), on, b, nx, from_lane((int)((q.x & 63u) << 2), T.h) - nx * b);
+  };
+
+  // Covered pixel e of each lane of mask `on`: ray hit, depth, ownership.
+  auto take = [&](uint32_t e, uint64_t on) {
+    const int src = (int)((e & 63u) << 2);
+    const uint32_t x = (e >> 6) & xm, y = (e >> ysh) & ym;
+    const int vsrc = (int)((e >> rsh) << 2);
+    const float b = from_lane(vsrc, eye_l);
+    const float rx = tx[x] - from_lane(vsrc, ks_l), ry = ty[y];
+    const float nx = from_lane(src, T.nx);
+    const float delta = from_lane(src, T.h) - nx * b;
+    const float den = (nx * rx + from_lane(src, T.ny) * ry) + from_lane(src, T.nz);
+    const float ux = from_lane(src, T.ux), wx = from_lane(src, T.wx);
+    const float bp = b - from_lane(src, T.p0x);
+    const float cu = ux * bp - from_lane(src, T.cu0);
+    const float cw = wx * bp - from_lane(src, T.cw0);
+    const float ur = (ux * rx + from_lane(src, T.uy) * ry) + from_lane(src, T.uz);
+    const float wr = (wx * rx + from_lane(src, T.wy) * ry) + from_lane(src, T.wz);
+    const float Z = delta / den;
+    const float sv = from_lane(src, T.sx) * (Z * ur + cu) + 0.5f;
+    const float tv = from_lane(src, T.sy) * (Z * wr + cw) + 0.5f;
+    const uint64_t m = on & __builtin_amdgcn_ballot_w64(Z > 0.0f) & __builtin_amdgcn_ballot_w64(Z < INFINITY) &
+                       ~__builtin_amdgcn_ballot_w64(sv < from_lane(src, s_lo)) &
+                       ~__builtin_amdgcn_ballot_w64(sv >= from_lane(src, s_hi)) &
+                       ~__builtin_amdgcn_ballot_w64(tv < from_lane(src, t_lo)) &
+                       ~__builtin_amdgcn_ballot_w64(tv >= from_lane(src, t_hi));
+    if (!m) return;
+    const bool own = __builtin_amdgcn_inverse_ballot_w64(m);
+    written += (uint32_t)__builtin_popcountll(m);
+    if (kPBR && own_queue) {
+      if (own) own_queue[on_n + lanes_below(m)] = make_uint2(e, __float_as_uint(Z));
+      on_n += (uint32_t)__builtin_popcountll(m);
+      if (on_n >= 64) {
+        wave_sync_lds();
+        const uint2 q = own_queue[lane], moved = own_queue[64 + lane];
+        wave_sync_lds();
+        on_n -= 64;
+        if ((uint32_t)lane < on_n) own_queue[lane] = moved;
+        emit_queued(q, true);
+      }
+    } else {
+      emit_key(e, Z, own, b, nx, delta);
+    }
+  };
+
+  // Pixel e of each lane of mask m is covered: queued, and 64 of them taken when there are as many.
+  auto push = [&](uint32_t e, uint64_t m) {
+    if (!m) return;
+    const bool mine = __builtin_amdgcn_inverse_ballot_w64(m);
+    if (kQuilt && !queue) {
+      take(mine ? e : (uint32_t)lane, m);
+      return;
+    }
+    if (mine) queue[qn + lanes_below(m)] = e;
+    qn += (uint32_t)__builtin_popcountll(m);
+    if (qn < 64) return;
+    wave_sync_lds();
+    const uint32_t te = queue[lane], moved = queue[64 + lane];
+    wave_sync_lds();
+    qn -= 64;
+    if ((uint32_t)lane < qn) queue[lane] = moved;
+    take(te, ~0ull);
+  };
+
+  for (; g0 < r_end; g0 += group) {
+    const int g1 = min(r_end, g0 + group);
+    const int rl = min(g0 + lane, r_end - 1);
+    eye_l = rg.eye[rl];
+    ks_l = rg.kshift[rl];
+    float b_next = table_f32(rg.eye, g0);  // the next view's eye offset, one iteration ahead
+    for (int r = g0; r < g1; ++r) {
+      const float b = b_next;
+      if (r + 1 < g1) b_next = table_f32(rg.eye, r + 1);
+      uint64_t act = alive_m;
+      if (!all_safe) act &= __builtin_amdgcn_ballot_w64(faces_eye(T.p0x, p0y2, p0z2, T.h - T.nx * b, b));
+      // splat box columns first: empty for about a third of the (point, view) pairs
+      const float c0 = cA[0] - b * cC[0], c1 = cA[1] - b * cC[1], c2 = cA[2] - b * cC[2], c3 = cA[3] - b * cC[3];
+      const float xmn = fminf(fminf(c0, c1), fminf(c2, c3)), xmx = fmaxf(fmaxf(c0, c1), fmaxf(c2, c3));
+      int32_t bx0 = (int32_t)ceilf(__builtin_amdgcn_fmed3f(xmn - 0.515625f, 0.0f, 8192.0f));
+      int32_t bx1 = (int32_t)floorf(__builtin_amdgcn_fmed3f(xmx - 0.484375f, -1.0f, x_last));
+      act &= __builtin_amdgcn_ballot_w64(bx0 <= bx1);
+      if (!act) continue;
+      // Q8 vertices, rounded to integers in the low mantissa bits (offset by kRoundBits): exact up to 2^22, that
+      // is 16384 px; beyond, still monotone, so far off every view (at most 4096 px wide) as before
+      const float x0 = va[0] - b * vc[0], x1 = va[1] - b * vc[1], x2 = va[2] - b * vc[2];
+      if (!all_safe)
+        act &= __builtin_amdgcn_ballot_w64(fabsf(x0) < kGuardQ8 && fabsf(x1) < kGuardQ8 && fabsf(x2) < kGuardQ8);
+      const int32_t q0 = __float_as_int(x0 + kRound), q1 = __float_as_int(x1 + kRound), q2 = __float_as_int(x2 + kRound);
+      const int32_t xmin = min(q0, min(q1, q2)), xmax = max(q0, max(q1, q2));
+      bx0 = max(bx0, (xmin - (kRoundBits - 127)) >> 8);
+      bx1 = min(bx1, (xmax - (kRoundBits + 128)) >> 8);
+      const int32_t w = bx1 - bx0 + 1;
+      act &= __builtin_amdgcn_ballot_w64(w > 0);
+      const int32_t pxq = 256 * bx0 + (128 + kRoundBits);
+      const int32_t dx0 = q1 - q0, dx1 = q2 - q1, dx2 = q0 - q2;
+      // edge functions at (bx0, by0), minus one where the edge does not own its ties: covered iff none is negative
+      int32_t R0 = mad24(ndy[0], pxq - q0, mad24(dx0, py[0], tie[0]));
+      int32_t R1 = mad24(ndy[1], pxq - q1, mad24(dx1, py[1], tie[1]));
+      int32_t R2 = mad24(ndy[2], pxq - q2, mad24(dx2, py[2], tie[2]));
+      // their sum is the doubled area (plus tsum) at every pixel
+      const uint64_t wide = tall_m | __builtin_amdgcn_ballot_w64(xmax - xmin > kSmallSpan) |
+                            __builtin_amdgcn_ballot_w64((int32_t)((uint32_t)R0 + (uint32_t)R1 + (uint32_t)R2) <= tsum);
+      // Boxes beyond kLaneBox pixels (and wide triangles) are walked by the
+      // whole wave, 64 pixels at a time, after the lanes' own boxes.
+      const int32_t npx = __mul24(w, nrows);
+      uint64_t heavy = act & (wide | __builtin_amdgcn_ballot_w64(npx > kLaneBox));
+      const uint32_t e0 = (uint32_t)((bx0 << 6) + (int32_t)((uint32_t)lane | ((uint32_t)by0 << ysh))) + ((uint32_t)(r - g0) << rsh);
+      int32_t rem = (__builtin_amdgcn_inverse_ballot_w64(act & ~heavy) ? npx : 0) - 1;  // pixels after this one
+      if (__builtin_amdgcn_ballot_w64(rem >= 0)) {
+        int32_t E0 = R0, E1 = R1, E2 = R2, cx = w;
+        uint32_t e = e0;
+        for (;;) {
+          push(e, __builtin_amdgcn_ballot_w64((E0 | E1 | E2 | rem) >= 0));
+          rem -= 1;
+          if (!__builtin_amdgcn_ballot_w64(rem >= 0)) break;
+          cx -= 1;
+          e += 64u;
+          E0 += ndy[0] << 8;
+          E1 += ndy[1] << 8;
+          E2 += ndy[2] << 8;
+          if (cx == 0) {  // the next row of the box
+            cx = w;
+            e += (1u << ysh) - ((uint32_t)w << 6);
+            E0 = R0 += dx0 << 8;
+            E1 = R1 += dx1 << 8;
+            E2 = R2 += dx2 << 8;
+          }
         }
       }
+      while (heavy) {
+        const int32_t hl = (int32_t)__builtin_ctzll(heavy);
+        heavy &= heavy - 1;
+        const int32_t hn = __builtin_amdgcn_readlane(npx, hl), hw = __builtin_amdgcn_readlane(w, hl);
+        const uint32_t he = (uint32_t)__builtin_amdgcn_readlane((int)e0, hl);
+        const int32_t wy = 256 * __builtin_amdgcn_readlane(by0, hl) + 128;
+        const int32_t qyw[3] = {wy - __builtin_amdgcn_readlane(py[0], hl), wy - __builtin_amdgcn_readlane(py[1], hl),
+                                wy - __builtin_amdgcn_readlane(py[2], hl)};
+        int32_t qx[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          const float ha = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(va[k]), hl));
+          const float hc = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(vc[k]), hl));
+          qx[k] = (int32_t)rintf(ha - b * hc);
+        }
+        const float inv = 1.0f / (float)hw;
+        for (int32_t k0 = 0; k0 < hn; k0 += 64) {
+          // pixel k of the box: row k / hw by the float reciprocal (k < 2^24, off by one at most)
+          const int32_t k = k0 + lane;
+          int32_t yq = (int32_t)((float)k * inv), xq = k - yq * hw;
+          if (xq < 0) { yq -= 1; xq += hw; }
+          else if (xq >= hw) { yq += 1; xq -= hw; }
+          const uint32_t e = he + ((uint32_t)xq << 6) + ((uint32_t)yq << ysh);
+          push(e, __builtin_amdgcn_ballot_w64(k < hn && covered_wide((int32_t)((e >> 6) & xm), (int32_t)((e >> ysh) & ym), qx, qyw)));
+        }
+      }
+    }
+    // what waits goes before the group's tables are replaced
+    if (qn) {
+      wave_sync_lds();
+      const uint32_t te = (uint32_t)lane < qn ? queue[lane] : 0u;
+      wave_sync_lds();
+      const uint64_t on = ~(~0ull << qn);
+      qn = 0;
+      take(te, on);
+    }
+    if (kPBR && on_n) {
+      wave_sync_lds();
+      const bool on = (uint32_t)lane < on_n;
+      const uint2 q = on ? own_queue[lane] : make_uint2(0u, 0u);
+      wave_sync_lds();
+      on_n = 0;
+      emit_queued(q, on);
     }
   }
 }
 
 // kMulti: points of several items (a batch); otherwise every point belongs to
-// items[0] and the item is read once.  kPBR: shaded colours;
-// held to 128 VGPRs (4 waves per SIMD instead of 3 at its natural 138), which
-// measured faster despite an 8-byte spill.  The batch instantiation keeps 139:
-// capped, it spills 40 bytes and slows down.
+// items[0] and the item is read once.  kPBR: shaded colours.
+// A wave takes 64 consecutive points and, when the frame has too few points to
+// occupy the chip, only a part of the views: with kFillWaves waves or more the
+// point set-up is not repeated, below that the view loop is split (a frame of
+// 20 thousand points is 315 waves of up to V dependent steps otherwise).
+constexpr uint32_t kFillWaves = 4096;
+
 template <bool kMulti, bool kPBR>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPBR && !kMulti ? 4 : 1))) k_splat(SplatArgs a) {
+__global__ void __launch_bounds__(256) k_splat(SplatArgs a) {
   if (a.gate && *a.gate == 0) return;
   extern __shared__ float ray_tab[];  // W column slopes, then H row slopes
+  __shared__ uint32_t queues[4][kSplatQueue];
+  __shared__ uint2 own_queues[kPBR ? 4 : 1][kPBR ? kSplatQueue : 1];
   const Rig& trg = a.table_rig;
   float* tx = ray_tab;
   float* ty = ray_tab + trg.W;
@@ -908,16 +1141,33 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPBR &
   for (int k = threadIdx.x; k < trg.H; k += blockDim.x) ty[k] = ((float)k + 0.5f - trg.cy) / trg.fy;
   __syncthreads();
   const uint64_t npts = imin((int64_t)*a.n_points, a.cap);
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint32_t* const queue = queues[wv];
+  uint2* const own_queue = kPBR ? own_queues[wv] : nullptr;
   const Item it0 = load_uniform(a.items);
   uint32_t written = 0;
-  for (uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; p < npts; p += stride) {
+  const uint64_t chunks = (npts + 63) >> 6;
+  const uint32_t V = (uint32_t)trg.n_views;
+  const uint32_t parts =
+      chunks >= kFillWaves || chunks == 0 ? 1u : min(V, (kFillWaves + (uint32_t)chunks - 1) / (uint32_t)chunks);
+  const uint32_t per = (V + parts - 1) / parts;  // views per part
+  for (uint64_t c = (uint64_t)blockIdx.x * 4 + wv; c < chunks * parts; c += (uint64_t)gridDim.x * 4) {
+    uint64_t chunk = c;
+    int r0 = 0, r1 = (int)V;
+    if (parts > 1) {  // fewer than kFillWaves chunks: 32 bits hold c
+      chunk = (uint32_t)c / parts;
+      r0 = (int)(((uint32_t)c - (uint32_t)chunk * parts) * per);
+      r1 = min((int)V, r0 + (int)per);
+      if (r0 >= r1) continue;
+    }
+    uint64_t p = chunk * 64 + (uint64_t)lane;
+    const bool valid = p < npts;
+    p = valid ? p : npts - 1;
     const Point pt = a.points[p];
-    const uint32_t tri = pt.tri_flags & 0x0FFFFFFFu, flags = pt.tri_flags >> 28;
-    const int32_t i = (int16_t)(pt.ij & 0xFFFFu), j = (int16_t)(pt.ij >> 16);
+    const uint32_t tri = pt.tri_flags & 0x0FFFFFFFu;
     if (!kMulti) {
       const TriRec T = a.rec[tri];
-      splat_point<kPBR>(it0, pt, T, flags, i, j, tx, ty, a, p, written);
+      splat_wave<kPBR, false>(it0, valid, p, pt, T, tx, ty, a, queue, own_queue, r0, r1, written);
       continue;
     }
     // points of one wave nearly always belong to one item: take the items one at
@@ -925,20 +1175,17 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPBR &
     // its trip count is the same in every lane and the body stays inside it.
     // Only the record's item is read before the loop (the whole record inside).
     const int32_t my = a.rec[tri].item;
-    uint64_t todo = __builtin_amdgcn_ballot_w64(true);
+    uint64_t todo = __builtin_amdgcn_ballot_w64(valid);
     while (todo) {
       const int32_t cur = __builtin_amdgcn_readlane(my, (int32_t)__builtin_ctzll(todo));
-      const bool mine = my == cur;
-      if (mine) {
-        const Item it = load_uniform(a.items + cur);
-        const TriRec T = a.rec[tri];
-        splat_point<kPBR>(it, pt, T, flags, i, j, tx, ty, a, p, written);
-      }
+      const bool mine = valid && my == cur;
+      const Item it = load_uniform(a.items + cur);
+      const TriRec T = a.rec[tri];
+      splat_wave<kPBR, false>(it, mine, p, pt, T, tx, ty, a, queue, own_queue, r0, r1, written);
       todo &= ~__builtin_amdgcn_ballot_w64(mine);
     }
   }
-  const uint64_t wsum = wave_sum((uint64_t)written);
-  if ((threadIdx.x & 63) == 0 && wsum) atomicAdd((unsigned long long*)&a.stats[STAT_WRITTEN], (unsigned long long)wsum);
+  if (lane == 0 && written) atomicAdd((unsigned long long*)&a.stats[STAT_WRITTEN], (unsigned long long)written);
 }
 
 // ------------------------------------------------------------------ a3: splat, row-band quilt
@@ -1122,24 +1369,23 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))
   const Item it0 = load_uniform(a.items + item);
   const int lane = threadIdx.x & 63;
   uint32_t written = 0;
+  uint32_t* const queue =
+      a.q_queue ? reinterpret_cast<uint32_t*>(ty + H) + (threadIdx.x >> 6) * kSplatQueue : nullptr;
   // the band's entries in chunks of 64, one chunk per wave at a time, taken
   // from an LDS counter as the waves free up: the tile ends when its last
   // chunk does, whatever the per-point work
   for (;;) {
     uint32_t c = 0;
     if (lane == 0) c = atomicAdd(&qnext, 64u);
-    c = (uint32_t)__shfl((int)c, 0, 64);
+    c = (uint32_t)__builtin_amdgcn_readfirstlane((int)c);
     if (c >= e1 - e0) break;
     const uint32_t e = e0 + c + (uint32_t)lane;
-    if (e < e1) {
-      const uint32_t p = a.q_entries[e];
-      const Point pt = a.points[p];
-      const uint32_t tri = pt.tri_flags & 0x0FFFFFFFu, flags = pt.tri_flags >> 28;
-      const int32_t i = (int16_t)(pt.ij & 0xFFFFu), j = (int16_t)(pt.ij >> 16);
-      const TriRec T = a.rec[tri];
-      qt.box = a.pbox + p;
-      splat_point<kPBR, true>(it0, pt, T, flags, i, j, tx, ty, a, p, written, &qt);
-    }
+    const bool valid = e < e1;
+    const uint32_t p = a.q_entries[valid ? e : e1 - 1];
+    const Point pt = a.points[p];
+    const TriRec T = a.rec[pt.tri_flags & 0x0FFFFFFFu];
+    qt.box = a.pbox + p;
+    splat_wave<kPBR, true>(it0, valid, p, pt, T, tx, ty, a, queue, nullptr, qt.r_lo, qt.r_hi, written, &qt);
   }
   __syncthreads();
   // the tile as RGBA8 (+ depth): one pixel row of one view per wave at a time
@@ -1156,8 +1402,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))
       if (a.out_depth) a.out_depth[o + x] = empty ? __uint_as_float(0x7f800000u) : __uint_as_float((uint32_t)(key >> 32));
     }
   }
-  const uint64_t wsum = wave_sum((uint64_t)written);
-  if (lane == 0 && wsum) atomicAdd((unsigned long long*)&a.stats[STAT_WRITTEN], (unsigned long long)wsum);
+  if (lane == 0 && written) atomicAdd((unsigned long long*)&a.stats[STAT_WRITTEN], (unsigned long long)written);
 }
 
 // ------------------------------------------------------------------ a3: splat, triangle-major
@@ -1205,12 +1450,6 @@ __device__ __forceinline__ PairData load_pair(const uint4 (*pw)[64], int o) {
 #pragma unroll
   for (int g = 0; g < kPairWords; ++g) w[g] = pw[g][o];
   return P;
-}
-
-__device__ __forceinline__ void wave_sync_lds() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // One covered pixel of pair Q: ray hit, owning cell, its splat rectangle and
@@ -1674,6 +1913,8 @@ size_t quilt_lds_bytes(int32_t rows, int32_t views, int32_t W, int32_t H) {
   return (size_t)rows * (size_t)views * (size_t)W * 8u + (size_t)(W + H) * 4u + kQuiltStaticLds;
 }
 
+size_t quilt_queue_bytes(int32_t block) { return (size_t)(block / 64) * kSplatQueue * sizeof(uint32_t); }
+
 void launch_quilt_bin(const QuiltBinArgs& a, hipStream_t s) {
   const unsigned g = (unsigned)imin(nblk(a.cap, kQChunk), 1024);
   k_qcount<<<g, 256, sizeof(uint32_t) * (size_t)a.bands, s>>>(a);
@@ -1693,7 +1934,8 @@ hipError_t prepare_quilt_kernels(size_t lds) {
 }
 
 hipError_t launch_splat_quilt(const SplatArgs& a, hipStream_t s) {
-  const size_t lds = quilt_lds_bytes(a.q_rows, a.q_views, a.table_rig.W, a.table_rig.H) - kQuiltStaticLds;
+  const size_t lds = quilt_lds_bytes(a.q_rows, a.q_views, a.table_rig.W, a.table_rig.H) - kQuiltStaticLds +
+                     (a.q_queue ? quilt_queue_bytes(a.q_block) : 0);
   const unsigned g = (unsigned)((a.q_bands + 7) / 8) * 8u * (unsigned)a.q_subsets;
   if (a.q_block == 512) {
     if (a.tm) k_splat_quilt<true, 512><<<g, 512, lds, s>>>(a);
