@@ -46,7 +46,7 @@ constexpr int64_t kNoAllocKeys = 1 << 21;
 constexpr size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 constexpr size_t kOffItem = 0;
 constexpr size_t kOffStats = kOffItem + align256(sizeof(Item));
-constexpr size_t kOffCounts = kOffStats + align256(8 * STAT_SLOTS);
+constexpr size_t kOffCounts = kOffStats + align256(8 * kStatWords);
 constexpr size_t kOffOffsets = kOffCounts + align256(4 * kNoAllocTris);
 constexpr size_t kOffTiles = kOffOffsets + align256(8 * kNoAllocTris);
 constexpr size_t kOffRec = kOffTiles + align256(8 * (kNoAllocTris / 256 + 1));
@@ -392,8 +392,8 @@ int prepare_frame_buffers(lfdpr_ctx* ctx, int64_t nt, bool pbr) {
     ctx->points_alloc = ctx->cap;
   }
   if (!ctx->d_stats) {
-    if (dalloc(ctx->d_stats, STAT_SLOTS) != hipSuccess) return fail(ctx, LFDPR_ENOMEM, "statistics");
-    if (hipMemset(ctx->d_stats, 0, STAT_SLOTS * sizeof(uint64_t)) != hipSuccess)
+    if (dalloc(ctx->d_stats, kStatWords) != hipSuccess) return fail(ctx, LFDPR_ENOMEM, "statistics");
+    if (hipMemset(ctx->d_stats, 0, kStatWords * sizeof(uint64_t)) != hipSuccess)
       return fail(ctx, LFDPR_EDEVICE, "clearing statistics");
   }
   if (pbr && (ctx->tm_cap < ctx->tri_cap || ctx->pmat_cap != ctx->cap)) {
@@ -573,7 +573,7 @@ int lfdpr_create(int device, void* stream, lfdpr_ctx** out) {
       ctx->max_lds = 0;  // no tile fits: the quilt order is refused
     }
   }
-  if (dalloc(ctx->d_stats, STAT_SLOTS) != hipSuccess || dalloc(ctx->d_item1, 1) != hipSuccess) {
+  if (dalloc(ctx->d_stats, kStatWords) != hipSuccess || dalloc(ctx->d_item1, 1) != hipSuccess) {
     dfree(ctx->d_stats);
     delete ctx;
     return LFDPR_ENOMEM;
@@ -588,7 +588,7 @@ int lfdpr_create(int device, void* stream, lfdpr_ctx** out) {
   }
   if (dalloc(ctx->d_lod_thr, 128) != hipSuccess ||
       hipMemcpy(ctx->d_lod_thr, thr, sizeof thr, hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemset(ctx->d_stats, 0, STAT_SLOTS * sizeof(uint64_t)) != hipSuccess) {
+      hipMemset(ctx->d_stats, 0, kStatWords * sizeof(uint64_t)) != hipSuccess) {
     lfdpr_destroy(ctx);
     return LFDPR_EDEVICE;
   }
@@ -984,7 +984,7 @@ int lfdpr_render_frame(lfdpr_ctx* ctx, int32_t scene_id, const float* model, uin
     HIPOK(hipMemcpy(ctx->d_item1, &one, sizeof one, hipMemcpyHostToDevice));
     std::memcpy(&ctx->h_item1, &one, sizeof one);
   }
-  launch_fill_u64(ctx->d_stats, STAT_SLOTS, 0ull, gen);
+  launch_fill_u64(ctx->d_stats, kStatWords, 0ull, gen);
   SetupArgs sa{};
   sa.items = ctx->d_item1;
   sa.n_items = 1;
@@ -1148,7 +1148,7 @@ int lfdpr_render_frame_noalloc(lfdpr_ctx* ctx, int32_t scene_id, const float* mo
   one.mat = nullptr;
   // the scratch keeps the last call's contents: statistics start at 0, keys at ~0
   launch_store_item(one, d_item, st);
-  launch_fill_u64(d_st, STAT_SLOTS, 0ull, st);
+  launch_fill_u64(d_st, kStatWords, 0ull, st);
   launch_fill_u64(d_keys, nkeys, ~0ull, st);
   SetupArgs sa{};
   sa.items = d_item;
@@ -1545,7 +1545,7 @@ hipEvent_t batch_gen(lfdpr_batch* b, hipStream_t st, bool timed) {
   lfdpr_ctx* ctx = b->ctx;
   const bool pbr = ctx->shading.mode == LFDPR_SHADE_PBR;
   auto ev = [&]() { return timed ? mark_on(ctx, st) : nullptr; };
-  launch_fill_u64(b->stats, STAT_SLOTS, 0ull, st);
+  launch_fill_u64(b->stats, kStatWords, 0ull, st);
   hipEvent_t e0 = ev();
   SetupArgs sa{};
   sa.items = b->d_items;
@@ -1779,7 +1779,7 @@ int lfdpr_batch_create(lfdpr_ctx* ctx, int32_t n, const int32_t* scene_ids, cons
          dalloc(b->tiles, (ntb + 255) / 256 + 1) == hipSuccess && dalloc(b->big, ntb) == hipSuccess &&
          dalloc(b->tris, ntb) == hipSuccess && dalloc(b->rows, (size_t)b->cap) == hipSuccess &&
          dalloc(b->pbox, (size_t)b->cap) == hipSuccess &&
-         dalloc(b->stats, STAT_SLOTS) == hipSuccess && dalloc(b->points, (size_t)b->cap) == hipSuccess &&
+         dalloc(b->stats, kStatWords) == hipSuccess && dalloc(b->points, (size_t)b->cap) == hipSuccess &&
          dalloc(b->d_items, n) == hipSuccess && dalloc(b->d_models, n) == hipSuccess &&
          hipHostMalloc((void**)&b->h_models, sizeof(Model) * n, hipHostMallocDefault) == hipSuccess;
   if (ok) {
@@ -1850,7 +1850,7 @@ int lfdpr_batch_set_frames_in_flight(lfdpr_batch* b, int32_t n) {
   if (ok)
     ok = dalloc(a.counts, ntb) == hipSuccess && dalloc(a.offsets, ntb) == hipSuccess && dalloc(a.rec, ntb) == hipSuccess &&
          dalloc(a.em, ntb) == hipSuccess && dalloc(a.tiles, (ntb + 255) / 256 + 1) == hipSuccess &&
-         dalloc(a.big, ntb) == hipSuccess && dalloc(a.stats, STAT_SLOTS) == hipSuccess &&
+         dalloc(a.big, ntb) == hipSuccess && dalloc(a.stats, kStatWords) == hipSuccess &&
          dalloc(a.tris, ntb) == hipSuccess && dalloc(a.rows, (size_t)b->cap) == hipSuccess &&
          dalloc(a.pbox, (size_t)b->cap) == hipSuccess &&
          dalloc(a.points, (size_t)b->cap) == hipSuccess && dalloc(a.d_models, b->n) == hipSuccess &&

@@ -10,6 +10,12 @@ namespace lfdpr {
 enum StatSlot { STAT_ACTIVE = 0, STAT_OVERFLOW = 1, STAT_POINT_VIEWS = 2, STAT_TOTAL = 3, STAT_BIG = 4,
                 STAT_WRITTEN = 5, STAT_EMITTING = 6, STAT_COVERED = 7, STAT_SLOTS = 8 };
 
+// The statistics buffer also holds the counters of the point splat's work
+// queues, a 128-byte line each, cleared with them at the start of a frame.
+constexpr int kWorkQueues = 64;
+constexpr int kWorkNext = 16;  // 64-bit words before the first counter
+constexpr int64_t kStatWords = kWorkNext + 16 * kWorkQueues;
+
 // One frame of one scene inside a (possibly single-element) batch.  Items share
 // the view size and projection (W, H, fovy, aspect); eye tables may differ.
 struct Item {

@@ -713,8 +713,8 @@ __device__ __forceinline__ void wave_sync_lds() {
 //                   (ds_bpermute), the view's from lanes that hold the tables;
 //   owned pixels    (kPBR) queued once more, so that shading -- four fifths of
 //                   the instructions there -- runs on full waves.
-// A box of more than kLaneBox pixels would hold its whole wave (one lane of a
-// grazing triangle took 1.5 ms): all lanes walk it, 64 pixels at a time.
+// A box of many pixels would hold its whole wave (one lane of a grazing
+// triangle took 1.5 ms): all lanes walk it, 64 pixels at a time.
 // Measured on a million-triangle frame (3.0M points, 48 views of 512 x 512)
 // against one lane carrying each pixel to its key: 8.3e8 -> 4.8e8 vector
 // instructions, 2.48 -> 1.17 ms.
@@ -725,21 +725,25 @@ __device__ __forceinline__ void wave_sync_lds() {
 // its area positive for an eye in front of it, so dy, the tie rule (an edge
 // owns its ties iff dy > 0, or dy == 0 and the third vertex lies below it) and
 // the distance of the first row from each vertex do not depend on the view.
-// With spans up to kSmallSpan (124 pixels) every term fits 32 bits and every
-// factor 24.  A larger triangle, or one whose snapped area is not positive in
-// this view, is walked by the whole wave with the exact 64-bit test
+// A step of one pixel changes E by a multiple of 256, so E >> 8 carries its
+// sign from pixel to pixel.  With spans up to kSmallSpan (124 pixels) E itself
+// fits 32 bits and every factor 24, up to kLargeSpan (1562 pixels) E >> 8 does,
+// in two parts.  A larger triangle, or one whose snapped area is not positive
+// in this view, is walked by the whole wave with the exact 64-bit test
 // (covered_wide).
 //
 // kQuilt: only the views and rows of tile *qt, keys in its LDS; the splat
 // rectangle's corners, rows and cell-centre depth come from the point's
 // PointBox (the same values, computed at emission).  queue == nullptr (a tile
 // that leaves no LDS for it): each lane takes its own covered pixel at once.
-constexpr int kSplatQueue = 128;        // entries: 63 waiting and 64 new ones at most
-constexpr int32_t kLaneBox = 16;        // pixels of a box that its lane walks alone
+constexpr int kSplatQueue = 191;        // entries: 63 waiting and 128 new ones at most
+constexpr int32_t kLaneSteps = 8;       // steps of two pixels that a lane walks alone
+constexpr int kOwnQueue = 128;          // 63 waiting and 64 new ones
 constexpr float kRound = 12582912.0f;    // 1.5 * 2^23: adding it rounds to an integer (ties to even) ...
 constexpr int32_t kRoundBits = 0x4B400000;  // ... held in the sum's bits, offset by this
 constexpr float kGuardQ8 = kGuard * 256.0f;
 constexpr int32_t kSmallSpan = 31744;   // Q8: |E| <= 2 * 31744^2 + one step < 2^31
+constexpr int32_t kLargeSpan = 400000;  // Q8: |E >> 8| <= 2 * 400000^2 / 256 + one step < 2^31
 
 // a * b + c with 24-bit factors
 __device__ __forceinline__ int32_t mad24(int32_t a, int32_t b, int32_t c) {
@@ -747,6 +751,8 @@ __device__ __forceinline__ int32_t mad24(int32_t a, int32_t b, int32_t c) {
   asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
   return d;
 }
+
+__device__ __forceinline__ int32_t mul24(int32_t a, int32_t b) { return __mul24(a, b); }
 
 __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
@@ -860,6 +866,7 @@ __device__ __forceinline__ void splat_wave(const Item& item, bool valid, uint64_
     tie[e] = (ndy[e] < 0 || (ndy[e] == 0 && qy[ec] > qy[e])) ? 0 : -1;
   }
   const uint64_t tall_m = __builtin_amdgcn_ballot_w64(ymax - ymin > kSmallSpan);
+  const uint64_t huge_m = __builtin_amdgcn_ballot_w64(ymax - ymin > kLargeSpan);
   const float x_last = (float)(rg.W - 1);
   const int32_t tsum = tie[0] + tie[1] + tie[2];
   // Facing and guard-band tests that hold for every eye are settled once: the
@@ -977,11 +984,10 @@ __device__ __forceinline__ void splat_wave(const Item& item, bool valid, uint64_
       if (own) own_queue[on_n + lanes_below(m)] = make_uint2(e, __float_as_uint(Z));
       on_n += (uint32_t)__builtin_popcountll(m);
       if (on_n >= 64) {
-        wave_sync_lds();
-        const uint2 q = own_queue[lane], moved = own_queue[64 + lane];
-        wave_sync_lds();
         on_n -= 64;
-        if ((uint32_t)lane < on_n) own_queue[lane] = moved;
+        wave_sync_lds();
+        const uint2 q = own_queue[on_n + lane];
+        wave_sync_lds();
         emit_queued(q, true);
       }
     } else {
@@ -989,23 +995,25 @@ __device__ __forceinline__ void splat_wave(const Item& item, bool valid, uint64_
     }
   };
 
-  // Pixel e of each lane of mask m is covered: queued, and 64 of them taken when there are as many.
-  auto push = [&](uint32_t e, uint64_t m) {
-    if (!m) return;
-    const bool mine = __builtin_amdgcn_inverse_ballot_w64(m);
+  // Pixel e of each lane of mask m0 and the next one of m1 are covered: queued, and taken 64 at a time.
+  auto push = [&](uint32_t e, uint64_t m0, uint64_t m1) {
+    if (!(m0 | m1)) return;
     if (kQuilt && !queue) {
-      take(mine ? e : (uint32_t)lane, m);
+      if (m0) take(__builtin_amdgcn_inverse_ballot_w64(m0) ? e : (uint32_t)lane, m0);
+      if (m1) take(__builtin_amdgcn_inverse_ballot_w64(m1) ? e + 64u : (uint32_t)lane, m1);
       return;
     }
-    if (mine) queue[qn + lanes_below(m)] = e;
-    qn += (uint32_t)__builtin_popcountll(m);
-    if (qn < 64) return;
-    wave_sync_lds();
-    const uint32_t te = queue[lane], moved = queue[64 + lane];
-    wave_sync_lds();
-    qn -= 64;
-    if ((uint32_t)lane < qn) queue[lane] = moved;
-    take(te, ~0ull);
+    const uint32_t n0 = (uint32_t)__builtin_popcountll(m0);
+    if (__builtin_amdgcn_inverse_ballot_w64(m0)) queue[qn + lanes_below(m0)] = e;
+    if (__builtin_amdgcn_inverse_ballot_w64(m1)) queue[qn + n0 + lanes_below(m1)] = e + 64u;
+    qn += n0 + (uint32_t)__builtin_popcountll(m1);
+    while (qn >= 64) {
+      qn -= 64;
+      wave_sync_lds();
+      const uint32_t te = queue[qn + lane];
+      wave_sync_lds();
+      take(te, ~0ull);
+    }
   };
 
   for (; g0 < r_end; g0 += group) {
@@ -1044,50 +1052,86 @@ __device__ __forceinline__ void splat_wave(const Item& item, bool valid, uint64_
       int32_t R1 = mad24(ndy[1], pxq - q1, mad24(dx1, py[1], tie[1]));
       int32_t R2 = mad24(ndy[2], pxq - q2, mad24(dx2, py[2], tie[2]));
       // their sum is the doubled area (plus tsum) at every pixel
-      const uint64_t wide = tall_m | __builtin_amdgcn_ballot_w64(xmax - xmin > kSmallSpan) |
-                            __builtin_amdgcn_ballot_w64((int32_t)((uint32_t)R0 + (uint32_t)R1 + (uint32_t)R2) <= tsum);
-      // Boxes beyond kLaneBox pixels (and wide triangles) are walked by the
-      // whole wave, 64 pixels at a time, after the lanes' own boxes.
-      const int32_t npx = __mul24(w, nrows);
-      uint64_t heavy = act & (wide | __builtin_amdgcn_ballot_w64(npx > kLaneBox));
+      uint64_t wide = __builtin_amdgcn_ballot_w64((int32_t)((uint32_t)R0 + (uint32_t)R1 + (uint32_t)R2) <= tsum);
+      R0 >>= 8;
+      R1 >>= 8;
+      R2 >>= 8;
+      const uint64_t large = act & (tall_m | __builtin_amdgcn_ballot_w64(xmax - xmin > kSmallSpan));
+      if (large) {
+        // E >> 8 from the whole and the fractional pixels of the distances
+        auto edge = [&](int32_t q, int32_t dx, int32_t nd, int32_t pye, int32_t te) {
+          const int32_t px = pxq - q;
+          return mad24(nd, (px + 128) >> 8, mul24(dx, (pye + 128) >> 8)) +
+                 (mad24(nd, ((px + 128) & 255) - 128, mad24(dx, ((pye + 128) & 255) - 128, te)) >> 8);
+        };
+        const bool lg = __builtin_amdgcn_inverse_ballot_w64(large);
+        const int32_t L0 = edge(q0, dx0, ndy[0], py[0], tie[0]), L1 = edge(q1, dx1, ndy[1], py[1], tie[1]),
+                      L2 = edge(q2, dx2, ndy[2], py[2], tie[2]);
+        R0 = lg ? L0 : R0;
+        R1 = lg ? L1 : R1;
+        R2 = lg ? L2 : R2;
+        // not positive here includes every triangle whose area is not
+        wide = (wide & ~large) | (large & __builtin_amdgcn_ballot_w64((int32_t)((uint32_t)L0 + (uint32_t)L1 + (uint32_t)L2) <= 0)) |
+               (large & (huge_m | __builtin_amdgcn_ballot_w64(xmax - xmin > kLargeSpan)));
+      }
+      // Lanes walk their own boxes, two pixels of a row at a time.  Boxes beyond
+      // some number of steps (and wide triangles) are left to the whole wave, 64
+      // pixels at a time: a step costs the wave a quarter of such a box, so the
+      // limit follows how many boxes exceed it.
+      const int32_t steps = __mul24((w + 1) >> 1, nrows);
+      uint64_t over = act & __builtin_amdgcn_ballot_w64(steps > kLaneSteps);
+      if (over) {
+        const uint64_t over4 = over & __builtin_amdgcn_ballot_w64(steps > 4 * kLaneSteps);
+        if (__builtin_popcountll(over) - __builtin_popcountll(over4) > 3 * kLaneSteps / 4) over = over4;
+      }
+      uint64_t heavy = (act & wide) | over;
       const uint32_t e0 = (uint32_t)((bx0 << 6) + (int32_t)((uint32_t)lane | ((uint32_t)by0 << ysh))) + ((uint32_t)(r - g0) << rsh);
-      int32_t rem = (__builtin_amdgcn_inverse_ballot_w64(act & ~heavy) ? npx : 0) - 1;  // pixels after this one
+      int32_t rem = (__builtin_amdgcn_inverse_ballot_w64(act & ~heavy) ? steps : 0) - 1;  // steps after this one
       if (__builtin_amdgcn_ballot_w64(rem >= 0)) {
-        int32_t E0 = R0, E1 = R1, E2 = R2, cx = w;
+        int32_t E0 = R0, E1 = R1, E2 = R2, cx = rem >= 0 ? w - 2 : 1 << 20;  // columns after the pair (none wraps that has no box)
         uint32_t e = e0;
         for (;;) {
-          push(e, __builtin_amdgcn_ballot_w64((E0 | E1 | E2 | rem) >= 0));
+          const uint64_t m0 = __builtin_amdgcn_ballot_w64((E0 | E1 | E2 | rem) >= 0);
+          E0 += ndy[0];
+          E1 += ndy[1];
+          E2 += ndy[2];
+          push(e, m0, __builtin_amdgcn_ballot_w64((E0 | E1 | E2 | rem | cx) >= 0));
           rem -= 1;
           if (!__builtin_amdgcn_ballot_w64(rem >= 0)) break;
-          cx -= 1;
-          e += 64u;
-          E0 += ndy[0] << 8;
-          E1 += ndy[1] << 8;
-          E2 += ndy[2] << 8;
-          if (cx == 0) {  // the next row of the box
-            cx = w;
-            e += (1u << ysh) - ((uint32_t)w << 6);
-            E0 = R0 += dx0 << 8;
-            E1 = R1 += dx1 << 8;
-            E2 = R2 += dx2 << 8;
+          cx -= 2;
+          e += 128u;
+          E0 += ndy[0];
+          E1 += ndy[1];
+          E2 += ndy[2];
+          if (cx < -1) {  // the next row of the box
+            cx = w - 2;
+            e += (1u << ysh) - (((uint32_t)w + 1u) >> 1 << 7);
+            E0 = R0 += dx0;
+            E1 = R1 += dx1;
+            E2 = R2 += dx2;
           }
         }
       }
       while (heavy) {
         const int32_t hl = (int32_t)__builtin_ctzll(heavy);
+        const bool exact = (wide >> hl) & 1;
         heavy &= heavy - 1;
-        const int32_t hn = __builtin_amdgcn_readlane(npx, hl), hw = __builtin_amdgcn_readlane(w, hl);
+        const int32_t hw = __builtin_amdgcn_readlane(w, hl), hn = hw * __builtin_amdgcn_readlane(nrows, hl);
         const uint32_t he = (uint32_t)__builtin_amdgcn_readlane((int)e0, hl);
+        int32_t qx[3], qyw[3];
         const int32_t wy = 256 * __builtin_amdgcn_readlane(by0, hl) + 128;
-        const int32_t qyw[3] = {wy - __builtin_amdgcn_readlane(py[0], hl), wy - __builtin_amdgcn_readlane(py[1], hl),
-                                wy - __builtin_amdgcn_readlane(py[2], hl)};
-        int32_t qx[3];
+        if (exact) {
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          const float ha = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(va[k]), hl));
-          const float hc = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(vc[k]), hl));
-          qx[k] = (int32_t)rintf(ha - b * hc);
+          for (int k = 0; k < 3; ++k) {
+            const float ha = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(va[k]), hl));
+            const float hc = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(vc[k]), hl));
+            qx[k] = (int32_t)rintf(ha - b * hc);
+            qyw[k] = wy - __builtin_amdgcn_readlane(py[k], hl);
+          }
         }
+        const int32_t H0 = __builtin_amdgcn_readlane(R0, hl), H1 = __builtin_amdgcn_readlane(R1, hl), H2 = __builtin_amdgcn_readlane(R2, hl);
+        const int32_t n0 = __builtin_amdgcn_readlane(ndy[0], hl), n1 = __builtin_amdgcn_readlane(ndy[1], hl), n2 = __builtin_amdgcn_readlane(ndy[2], hl);
+        const int32_t d0 = __builtin_amdgcn_readlane(dx0, hl), d1 = __builtin_amdgcn_readlane(dx1, hl), d2 = __builtin_amdgcn_readlane(dx2, hl);
         const float inv = 1.0f / (float)hw;
         for (int32_t k0 = 0; k0 < hn; k0 += 64) {
           // pixel k of the box: row k / hw by the float reciprocal (k < 2^24, off by one at most)
@@ -1096,7 +1140,13 @@ __device__ __forceinline__ void splat_wave(const Item& item, bool valid, uint64_
           if (xq < 0) { yq -= 1; xq += hw; }
           else if (xq >= hw) { yq += 1; xq -= hw; }
           const uint32_t e = he + ((uint32_t)xq << 6) + ((uint32_t)yq << ysh);
-          push(e, __builtin_amdgcn_ballot_w64(k < hn && covered_wide((int32_t)((e >> 6) & xm), (int32_t)((e >> ysh) & ym), qx, qyw)));
+          bool in;
+          if (exact)
+            in = covered_wide((int32_t)((e >> 6) & xm), (int32_t)((e >> ysh) & ym), qx, qyw);
+          else
+            in = ((H0 + mul24(n0, xq) + mul24(d0, yq)) | (H1 + mul24(n1, xq) + mul24(d1, yq)) |
+                  (H2 + mul24(n2, xq) + mul24(d2, yq))) >= 0;
+          push(e, __builtin_amdgcn_ballot_w64(k < hn && in), 0);
         }
       }
     }
@@ -1122,18 +1172,35 @@ __device__ __forceinline__ void splat_wave(const Item& item, bool valid, uint64_
 
 // kMulti: points of several items (a batch); otherwise every point belongs to
 // items[0] and the item is read once.  kPBR: shaded colours.
-// A wave takes 64 consecutive points and, when the frame has too few points to
-// occupy the chip, only a part of the views: with kFillWaves waves or more the
-// point set-up is not repeated, below that the view loop is split (a frame of
-// 20 thousand points is 315 waves of up to V dependent steps otherwise).
-constexpr uint32_t kFillWaves = 4096;
+// Work items are 64 consecutive points (a chunk) and the views, or a part of
+// the views when the frame has fewer than kFillItems chunks (one of 20 thousand
+// points is 315 waves of up to V dependent steps otherwise; the point set-up is
+// repeated for each part).  Waves draw items from kWorkQueues counters, each
+// wave from one of them: with a fixed stride the chip waits for its slowest
+// waves for a third of the launch, as items of 60 us at the median take 190 at
+// the 99th and 410 at the last percentile; one counter for all hands out only
+// some 60 items in a microsecond.  Measured (frames of 0.65M points, 25 views
+// of 317 x 253, and 3.0M points, 48 views of 512 x 512): the frame 450 -> 420
+// and 1577 -> 1483 us.  8192 items: 440 and 1505, 65536: 438 and 1455, 131072:
+// 483 and 1459 us.
+constexpr uint32_t kFillItems = 32768;
 
 template <bool kMulti, bool kPBR>
 __global__ void __launch_bounds__(256) k_splat(SplatArgs a) {
   if (a.gate && *a.gate == 0) return;
   extern __shared__ float ray_tab[];  // W column slopes, then H row slopes
   __shared__ uint32_t queues[4][kSplatQueue];
-  __shared__ uint2 own_queues[kPBR ? 4 : 1][kPBR ? kSplatQueue : 1];
+  __shared__ uint2 own_queues[kPBR ? 4 : 1][kPBR ? kOwnQueue : 1];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t queues_n = min((uint32_t)kWorkQueues, gridDim.x * 4);  // every queue has a wave
+  const uint32_t wq = (blockIdx.x * 4 + (uint32_t)wv) % queues_n;
+  uint32_t* const next = reinterpret_cast<uint32_t*>(a.stats + kWorkNext + 16 * wq);
+  auto draw = [&]() {  // the next item of this wave's queue
+    uint32_t k = 0;
+    if (lane == 0) k = atomicAdd(next, 1u);
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)k) * queues_n + wq;
+  };
+  uint32_t c = draw();
   const Rig& trg = a.table_rig;
   float* tx = ray_tab;
   float* ty = ray_tab + trg.W;
@@ -1141,33 +1208,23 @@ __global__ void __launch_bounds__(256) k_splat(SplatArgs a) {
   for (int k = threadIdx.x; k < trg.H; k += blockDim.x) ty[k] = ((float)k + 0.5f - trg.cy) / trg.fy;
   __syncthreads();
   const uint64_t npts = imin((int64_t)*a.n_points, a.cap);
-  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint32_t* const queue = queues[wv];
   uint2* const own_queue = kPBR ? own_queues[wv] : nullptr;
   const Item it0 = load_uniform(a.items);
   uint32_t written = 0;
-  const uint64_t chunks = (npts + 63) >> 6;
-  const uint32_t V = (uint32_t)trg.n_views;
-  const uint32_t parts =
-      chunks >= kFillWaves || chunks == 0 ? 1u : min(V, (kFillWaves + (uint32_t)chunks - 1) / (uint32_t)chunks);
-  const uint32_t per = (V + parts - 1) / parts;  // views per part
-  for (uint64_t c = (uint64_t)blockIdx.x * 4 + wv; c < chunks * parts; c += (uint64_t)gridDim.x * 4) {
-    uint64_t chunk = c;
-    int r0 = 0, r1 = (int)V;
-    if (parts > 1) {  // fewer than kFillWaves chunks: 32 bits hold c
-      chunk = (uint32_t)c / parts;
-      r0 = (int)(((uint32_t)c - (uint32_t)chunk * parts) * per);
-      r1 = min((int)V, r0 + (int)per);
-      if (r0 >= r1) continue;
-    }
-    uint64_t p = chunk * 64 + (uint64_t)lane;
+  const uint32_t chunks = (uint32_t)((npts + 63) >> 6), V = (uint32_t)trg.n_views;
+  const uint32_t want = chunks >= kFillItems || chunks == 0 ? 1u : min(V, (kFillItems + chunks - 1) / chunks);
+  const uint32_t per = (V + want - 1) / want, parts = (V + per - 1) / per;  // views per item, items per chunk
+  for (; c < chunks * parts; c = draw()) {
+    const uint32_t chunk = c / parts, r0 = (c - chunk * parts) * per, r1 = min(V, r0 + per);
+    uint64_t p = (uint64_t)chunk * 64 + (uint64_t)lane;
     const bool valid = p < npts;
     p = valid ? p : npts - 1;
     const Point pt = a.points[p];
     const uint32_t tri = pt.tri_flags & 0x0FFFFFFFu;
     if (!kMulti) {
       const TriRec T = a.rec[tri];
-      splat_wave<kPBR, false>(it0, valid, p, pt, T, tx, ty, a, queue, own_queue, r0, r1, written);
+      splat_wave<kPBR, false>(it0, valid, p, pt, T, tx, ty, a, queue, own_queue, (int)r0, (int)r1, written);
       continue;
     }
     // points of one wave nearly always belong to one item: take the items one at
@@ -1181,7 +1238,7 @@ __global__ void __launch_bounds__(256) k_splat(SplatArgs a) {
       const bool mine = valid && my == cur;
       const Item it = load_uniform(a.items + cur);
       const TriRec T = a.rec[tri];
-      splat_wave<kPBR, false>(it, mine, p, pt, T, tx, ty, a, queue, own_queue, r0, r1, written);
+      splat_wave<kPBR, false>(it, mine, p, pt, T, tx, ty, a, queue, own_queue, (int)r0, (int)r1, written);
       todo &= ~__builtin_amdgcn_ballot_w64(mine);
     }
   }
@@ -1880,6 +1937,9 @@ void launch_emit(const EmitArgs& a, int fetch_blocks, hipStream_t s) {
     k_fetch<false, false><<<fetch_blocks, 256, 0, s>>>(a);
 }
 
+// Four workgroups of the point splat fit a CU; more would find their queues empty.
+constexpr int kSplatGrid = 1024;
+
 void launch_splat(const SplatArgs& a, int grid_blocks, hipStream_t s) {
   size_t lds = sizeof(float) * (size_t)(a.table_rig.W + a.table_rig.H);
   if (a.pbox && !a.tm) {
@@ -1889,6 +1949,7 @@ void launch_splat(const SplatArgs& a, int grid_blocks, hipStream_t s) {
       k_splat_tv<false><<<grid_blocks, 256, lds, s>>>(a);
     return;
   }
+  grid_blocks = grid_blocks < kSplatGrid ? grid_blocks : kSplatGrid;
   if (a.n_items > 1 && a.tm)
     k_splat<true, true><<<grid_blocks, 256, lds, s>>>(a);
   else if (a.n_items > 1)

@@ -78,3 +78,21 @@ def test_splat_passes_match_the_oracle(torch_cuda, W, H, V, tex, quilt, pbr):
     assert st["written_px"] == o["stats"]["fragments"] - o["stats"]["misses"]
     np.testing.assert_array_equal(views.cpu().numpy().view(np.uint32), o["rgba"])
     np.testing.assert_array_equal(depth.cpu().numpy().view(np.uint32), o["depth"].view(np.uint32))
+
+
+@pytest.mark.parametrize("blocks", [1, 5, 15, 16, 17, 1024, 5000])
+def test_every_work_queue_is_drawn(torch_cuda, blocks):
+    """Frames of one chunk of points and of many, under grids with fewer waves than work queues and with more."""
+    from paper_2601_19901_amd import lfdpr
+    R = lfdpr.Renderer(0)
+    R.set_launch(blocks, 0)
+    for scene, V in ((_soup(5, 1, 40, 30, 4), 3), (_soup(6, 60, 130, 70, 64), 13)):
+        vp = scenes.ViewParams(V=V, W=130, H=70, fovy_deg=30.0, aspect=1.6, D=10.0, cone_deg=40.0, znear=0.5)
+        model = scenes.model_matrix(3, 10.0)
+        o = O.render(scene, vp, model)
+        R.set_views(vp)
+        views, depth = R.alloc_views(with_depth=True)
+        R.render_frame(R.upload_scene(scene), model, views, depth)
+        assert R.stats()["written_px"] == o["stats"]["fragments"] - o["stats"]["misses"]
+        np.testing.assert_array_equal(views.cpu().numpy().view(np.uint32), o["rgba"])
+        np.testing.assert_array_equal(depth.cpu().numpy().view(np.uint32), o["depth"].view(np.uint32))
