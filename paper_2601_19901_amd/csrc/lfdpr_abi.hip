@@ -49,7 +49,7 @@ constexpr size_t kOffStats = kOffItem + align256(sizeof(Item));
 constexpr size_t kOffCounts = kOffStats + align256(8 * kStatWords);
 constexpr size_t kOffOffsets = kOffCounts + align256(4 * kNoAllocTris);
 constexpr size_t kOffTiles = kOffOffsets + align256(8 * kNoAllocTris);
-constexpr size_t kOffRec = kOffTiles + align256(8 * (kNoAllocTris / 256 + 1));
+constexpr size_t kOffRec = kOffTiles + align256(8 * tile_sum_len(kNoAllocTris));
 constexpr size_t kOffEm = kOffRec + align256(sizeof(TriRec) * kNoAllocTris);
 constexpr size_t kOffBig = kOffEm + align256(sizeof(TriEmit) * kNoAllocTris);
 constexpr size_t kOffTris = kOffBig + align256(4 * kNoAllocTris);
@@ -422,7 +422,7 @@ int ensure_tri_buffers(lfdpr_ctx* ctx, int64_t nt) {
   dfree(ctx->d_tris);
   if (dalloc(ctx->d_counts, n) != hipSuccess || dalloc(ctx->d_offsets, n) != hipSuccess ||
       dalloc(ctx->d_rec, n) != hipSuccess || dalloc(ctx->d_em, n) != hipSuccess ||
-      dalloc(ctx->d_tiles, (n + 255) / 256 + 1) != hipSuccess || dalloc(ctx->d_big, n) != hipSuccess ||
+      dalloc(ctx->d_tiles, tile_sum_len(n)) != hipSuccess || dalloc(ctx->d_big, n) != hipSuccess ||
       dalloc(ctx->d_tris, n) != hipSuccess) {
     ctx->tri_cap = 0;
     return fail(ctx, LFDPR_ENOMEM, "per-triangle buffers");
@@ -1003,7 +1003,7 @@ int lfdpr_render_frame(lfdpr_ctx* ctx, int32_t scene_id, const float* model, uin
   sa.big = ctx->d_big;
   sa.n_big = ctx->d_stats + STAT_BIG;
   hipEvent_t e0 = mark_on(ctx, gen);
-  launch_tri_setup(sa, quilt, gen);
+  launch_tri_setup(sa, gen);
   hipEvent_t e1 = mark_on(ctx, gen);
   launch_scan(ctx->d_tiles, s.nt, ctx->d_stats + STAT_TOTAL, gen);
   hipEvent_t e2 = mark_on(ctx, gen);
@@ -1167,7 +1167,7 @@ int lfdpr_render_frame_noalloc(lfdpr_ctx* ctx, int32_t scene_id, const float* mo
   sa.tile_sum = d_tiles;
   sa.big = d_big;
   sa.n_big = d_st + STAT_BIG;
-  launch_tri_setup(sa, false, st);
+  launch_tri_setup(sa, st);
   launch_scan(d_tiles, s.nt, d_st + STAT_TOTAL, st);
   EmitArgs ea{};
   ea.items = d_item;
@@ -1561,7 +1561,7 @@ hipEvent_t batch_gen(lfdpr_batch* b, hipStream_t st, bool timed) {
   sa.tile_sum = b->tiles;
   sa.big = b->big;
   sa.n_big = b->stats + STAT_BIG;
-  launch_tri_setup(sa, b->splat_order == LFDPR_SPLAT_QUILT, st);
+  launch_tri_setup(sa, st);
   hipEvent_t e1 = ev();
   launch_scan(b->tiles, b->nt, b->stats + STAT_TOTAL, st);
   hipEvent_t e2 = ev();
@@ -1776,7 +1776,7 @@ int lfdpr_batch_create(lfdpr_ctx* ctx, int32_t n, const int32_t* scene_ids, cons
   if (ok)
     ok = dalloc(b->keys, (size_t)(b->per_item_px * n)) == hipSuccess && dalloc(b->counts, ntb) == hipSuccess &&
          dalloc(b->offsets, ntb) == hipSuccess && dalloc(b->rec, ntb) == hipSuccess && dalloc(b->em, ntb) == hipSuccess &&
-         dalloc(b->tiles, (ntb + 255) / 256 + 1) == hipSuccess && dalloc(b->big, ntb) == hipSuccess &&
+         dalloc(b->tiles, tile_sum_len(ntb)) == hipSuccess && dalloc(b->big, ntb) == hipSuccess &&
          dalloc(b->tris, ntb) == hipSuccess && dalloc(b->rows, (size_t)b->cap) == hipSuccess &&
          dalloc(b->pbox, (size_t)b->cap) == hipSuccess &&
          dalloc(b->stats, kStatWords) == hipSuccess && dalloc(b->points, (size_t)b->cap) == hipSuccess &&
@@ -1849,7 +1849,7 @@ int lfdpr_batch_set_frames_in_flight(lfdpr_batch* b, int32_t n) {
          hipEventCreateWithFlags(&b->ev_spl[k], hipEventDisableTiming) == hipSuccess;
   if (ok)
     ok = dalloc(a.counts, ntb) == hipSuccess && dalloc(a.offsets, ntb) == hipSuccess && dalloc(a.rec, ntb) == hipSuccess &&
-         dalloc(a.em, ntb) == hipSuccess && dalloc(a.tiles, (ntb + 255) / 256 + 1) == hipSuccess &&
+         dalloc(a.em, ntb) == hipSuccess && dalloc(a.tiles, tile_sum_len(ntb)) == hipSuccess &&
          dalloc(a.big, ntb) == hipSuccess && dalloc(a.stats, kStatWords) == hipSuccess &&
          dalloc(a.tris, ntb) == hipSuccess && dalloc(a.rows, (size_t)b->cap) == hipSuccess &&
          dalloc(a.pbox, (size_t)b->cap) == hipSuccess &&

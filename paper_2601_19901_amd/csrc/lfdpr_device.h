@@ -210,28 +210,81 @@ LF_HD bool may_be_seen(const Rig& rg, const TriRec& R) {
   return true;
 }
 
+// Correctly rounded binary32 quotients and roots for operands in the middle of
+// the range (|a| zero or in 2^-100 .. 2^100, |b| in 2^-100 .. 2^100, their
+// quotient in 2^-100 .. 2^100, x zero or in 2^-90 .. 2^90):
+// the reciprocal, two residual corrections and, for the root, the choice among
+// three neighbours by their residuals, which is what `/` and sqrtf come to there
+// without their scaling and special cases.  A divisor's reciprocal is shared
+// by all of its quotients.  Host: the plain operators.
+struct Divisor {
+  float b, y;
+};
+LF_HD Divisor divisor(float b) {
+#ifdef __HIP_DEVICE_COMPILE__
+  const float y = __builtin_amdgcn_rcpf(b);
+  return Divisor{b, __builtin_fmaf(__builtin_fmaf(-b, y, 1.0f), y, y)};
+#else
+  return Divisor{b, 0.0f};
+#endif
+}
+LF_HD float quotient(float a, Divisor d) {
+#ifdef __HIP_DEVICE_COMPILE__
+  float q = a * d.y;
+  q = __builtin_fmaf(__builtin_fmaf(-d.b, q, a), d.y, q);
+  return __builtin_fmaf(__builtin_fmaf(-d.b, q, a), d.y, q);
+#else
+  return a / d.b;
+#endif
+}
+LF_HD float root(float x) {
+#ifdef __HIP_DEVICE_COMPILE__
+  const float s = __builtin_amdgcn_sqrtf(x);  // within one unit in the last place
+  const float lo = __uint_as_float(__float_as_uint(s) - 1u), hi = __uint_as_float(__float_as_uint(s) + 1u);
+  const float rl = __builtin_fmaf(-lo, s, x), rh = __builtin_fmaf(-hi, s, x);
+  const float r = rl <= 0.0f ? lo : s;
+  return rh > 0.0f ? hi : r;
+#else
+  return sqrtf(x);
+#endif
+}
+
 // Point of triangle abc nearest to p, by the Voronoi regions of its vertices,
-// edges and face (Ericson, Real-Time Collision Detection, Sec. 5.1.5).
+// edges and face (Ericson, Real-Time Collision Detection, Sec. 5.1.5): the
+// region gives the numerator and denominator of one quotient (1 / the sum of
+// areas on the face), so that lanes in different regions divide together.
+// kPlain: by quotient() where its operands are in the middle of the range.
+template <bool kPlain>
 LF_HD F3 nearest_on_triangle(F3 p, F3 a, F3 b, F3 c) {
-  F3 ab = sub3(b, a), ac = sub3(c, a);
-  F3 ap = sub3(p, a);
-  float d1 = dot3(ab, ap), d2 = dot3(ac, ap);
-  if (d1 <= 0.0f && d2 <= 0.0f) return a;
-  F3 bp = sub3(p, b);
-  float d3 = dot3(ab, bp), d4 = dot3(ac, bp);
-  if (d3 >= 0.0f && d4 <= d3) return b;
-  float vc = d1 * d4 - d3 * d2;
-  if (vc <= 0.0f && d1 >= 0.0f && d3 <= 0.0f) return axpy3(a, d1 / (d1 - d3), ab);
-  F3 cp = sub3(p, c);
-  float d5 = dot3(ab, cp), d6 = dot3(ac, cp);
-  if (d6 >= 0.0f && d5 <= d6) return c;
-  float vb = d5 * d2 - d1 * d6;
-  if (vb <= 0.0f && d2 >= 0.0f && d6 <= 0.0f) return axpy3(a, d2 / (d2 - d6), ac);
-  float va = d3 * d6 - d5 * d4;
-  float e43 = d4 - d3, e56 = d5 - d6;
-  if (va <= 0.0f && e43 >= 0.0f && e56 >= 0.0f) return axpy3(b, e43 / (e43 + e56), sub3(c, b));
-  float inv = 1.0f / ((va + vb) + vc);
-  return axpy3(axpy3(a, vb * inv, ab), vc * inv, ac);
+  const F3 ab = sub3(b, a), ac = sub3(c, a);
+  const F3 ap = sub3(p, a), bp = sub3(p, b), cp = sub3(p, c);
+  const float d1 = dot3(ab, ap), d2 = dot3(ac, ap);
+  const float d3 = dot3(ab, bp), d4 = dot3(ac, bp);
+  const float d5 = dot3(ab, cp), d6 = dot3(ac, cp);
+  const float vc = d1 * d4 - d3 * d2, vb = d5 * d2 - d1 * d6, va = d3 * d6 - d5 * d4;
+  const float e43 = d4 - d3, e56 = d5 - d6;
+  const bool at_a = d1 <= 0.0f && d2 <= 0.0f;
+  const bool at_b = d3 >= 0.0f && d4 <= d3;
+  const bool on_ab = vc <= 0.0f && d1 >= 0.0f && d3 <= 0.0f;
+  const bool at_c = d6 >= 0.0f && d5 <= d6;
+  const bool on_ac = vb <= 0.0f && d2 >= 0.0f && d6 <= 0.0f;
+  const bool on_bc = va <= 0.0f && e43 >= 0.0f && e56 >= 0.0f;
+  // the first region that applies, in this order
+  if (at_a) return a;
+  if (at_b) return b;
+  if (!on_ab && at_c) return c;
+  float num, den;
+  if (on_ab) { num = d1; den = d1 - d3; }
+  else if (on_ac) { num = d2; den = d2 - d6; }
+  else if (on_bc) { num = e43; den = e43 + e56; }
+  else { num = 1.0f; den = (va + vb) + vc; }
+  float q;
+  if (kPlain && num > 0x1p-100f && den > 0x1p-100f && den < 0x1p100f) q = quotient(num, divisor(den));
+  else q = num / den;
+  if (on_ab) return axpy3(a, q, ab);
+  if (on_ac) return axpy3(a, q, ac);
+  if (on_bc) return axpy3(b, q, sub3(c, b));
+  return axpy3(axpy3(a, vb * q, ab), vc * q, ac);
 }
 
 // ---------------------------------------------------------------- lattice

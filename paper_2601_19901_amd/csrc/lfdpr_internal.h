@@ -56,7 +56,7 @@ struct SetupArgs {
   int32_t* dbgi;   // optional nt*8
   uint64_t* stats;
   TriMat* tm;      // physically based mode: per-triangle material records; else null
-  uint64_t* tile_sum;  // per workgroup (256 triangles): the sum of their counts
+  uint64_t* tile_sum;  // per workgroup (256 / setup_lanes(nt) triangles): the sum of their counts
   uint32_t* big;       // triangles with more than kBigCells cells (capacity nt)
   uint64_t* n_big;     // and their number
 };
@@ -67,7 +67,8 @@ struct EmitArgs {
   const uint32_t* big;       // triangles emitted cooperatively, queued by the set-up
   const uint64_t* n_big;
   const uint32_t* counts;
-  const uint64_t* tile_base;  // exclusive point offset of each tile of 256 triangles
+  const uint64_t* tile_base;  // exclusive point offset of each set-up workgroup's triangles
+  int32_t tile_step;          // entries of tile_base per emission tile (256 triangles)
   uint64_t* offsets;          // written: first point of each triangle
   const TriEmit* em;
   Point* points;
@@ -166,9 +167,10 @@ void launch_fill_u64(uint64_t* p, int64_t n, uint64_t v, hipStream_t s);
 void launch_store_item(const Item& it, Item* dst, hipStream_t s);
 void launch_export_stats(const uint64_t* st, int64_t cap, int64_t* out, hipStream_t s);
 void launch_build_mip(const uint32_t* src, uint32_t* dst, int s, hipStream_t st);
-// lean: the set-up form that stores its records before the lattice count
-// (fewer registers; used beside the quilt splat)
-void launch_tri_setup(const SetupArgs& a, bool lean, hipStream_t s);
+// Lanes of the set-up per triangle, and entries of tile_sum for nt triangles.
+int setup_lanes(int64_t nt);
+constexpr int64_t tile_sum_len(int64_t nt) { return (nt + 31) / 32 + 1; }
+void launch_tri_setup(const SetupArgs& a, hipStream_t s);
 // tile sums (written by the set-up) -> exclusive tile bases, and the total
 void launch_scan(uint64_t* tile_sum, int64_t nt, uint64_t* total, hipStream_t s);
 void launch_emit(const EmitArgs& a, int fetch_blocks, hipStream_t s);
