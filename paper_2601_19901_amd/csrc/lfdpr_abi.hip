@@ -49,7 +49,7 @@ constexpr size_t kOffStats = kOffItem + align256(sizeof(Item));
 constexpr size_t kOffCounts = kOffStats + align256(8 * kStatWords);
 constexpr size_t kOffOffsets = kOffCounts + align256(4 * kNoAllocTris);
 constexpr size_t kOffTiles = kOffOffsets + align256(8 * kNoAllocTris);
-constexpr size_t kOffRec = kOffTiles + align256(8 * tile_sum_len(kNoAllocTris));
+constexpr size_t kOffRec = kOffTiles + align256(16 * tile_sum_len(kNoAllocTris));
 constexpr size_t kOffEm = kOffRec + align256(sizeof(TriRec) * kNoAllocTris);
 constexpr size_t kOffBig = kOffEm + align256(sizeof(TriEmit) * kNoAllocTris);
 constexpr size_t kOffTris = kOffBig + align256(4 * kNoAllocTris);
@@ -238,6 +238,14 @@ void free_scene(SceneDev& s) {
   dfree(s.mat);
 }
 
+// Adds the lines' shares of the written and covered pixels to their totals.
+void add_stat_lines(uint64_t* st) {
+  for (int k = 0; k < kWorkQueues; ++k) {
+    st[STAT_WRITTEN] += st[kStatLines + LINE_WORDS * k + LINE_WRITTEN];
+    st[STAT_COVERED] += st[kStatLines + LINE_WORDS * k + LINE_COVERED];
+  }
+}
+
 // Waits for everything the context enqueued, on its stream and its side stream.
 hipError_t sync_all(lfdpr_ctx* ctx) {
   hipError_t e = hipStreamSynchronize(ctx->stream);
@@ -422,7 +430,7 @@ int ensure_tri_buffers(lfdpr_ctx* ctx, int64_t nt) {
   dfree(ctx->d_tris);
   if (dalloc(ctx->d_counts, n) != hipSuccess || dalloc(ctx->d_offsets, n) != hipSuccess ||
       dalloc(ctx->d_rec, n) != hipSuccess || dalloc(ctx->d_em, n) != hipSuccess ||
-      dalloc(ctx->d_tiles, tile_sum_len(n)) != hipSuccess || dalloc(ctx->d_big, n) != hipSuccess ||
+      dalloc(ctx->d_tiles, 2 * tile_sum_len(n)) != hipSuccess || dalloc(ctx->d_big, n) != hipSuccess ||
       dalloc(ctx->d_tris, n) != hipSuccess) {
     ctx->tri_cap = 0;
     return fail(ctx, LFDPR_ENOMEM, "per-triangle buffers");
@@ -1000,12 +1008,13 @@ int lfdpr_render_frame(lfdpr_ctx* ctx, int32_t scene_id, const float* model, uin
   sa.stats = ctx->d_stats;
   sa.tm = pbr ? ctx->d_tm : nullptr;
   sa.tile_sum = ctx->d_tiles;
+  sa.tile_stat = ctx->d_tiles + tile_sum_len(s.nt);
   sa.big = ctx->d_big;
   sa.n_big = ctx->d_stats + STAT_BIG;
   hipEvent_t e0 = mark_on(ctx, gen);
   launch_tri_setup(sa, gen);
   hipEvent_t e1 = mark_on(ctx, gen);
-  launch_scan(ctx->d_tiles, s.nt, ctx->d_stats + STAT_TOTAL, gen);
+  launch_scan(sa.tile_sum, sa.tile_stat, s.nt, ctx->d_stats, gen);
   hipEvent_t e2 = mark_on(ctx, gen);
   EmitArgs ea{};
   ea.items = ctx->d_item1;
@@ -1165,10 +1174,11 @@ int lfdpr_render_frame_noalloc(lfdpr_ctx* ctx, int32_t scene_id, const float* mo
   sa.stats = d_st;
   sa.tm = nullptr;
   sa.tile_sum = d_tiles;
+  sa.tile_stat = d_tiles + tile_sum_len(s.nt);
   sa.big = d_big;
   sa.n_big = d_st + STAT_BIG;
   launch_tri_setup(sa, st);
-  launch_scan(d_tiles, s.nt, d_st + STAT_TOTAL, st);
+  launch_scan(sa.tile_sum, sa.tile_stat, s.nt, d_st, st);
   EmitArgs ea{};
   ea.items = d_item;
   ea.nt = s.nt;
@@ -1256,10 +1266,11 @@ int lfdpr_angular_filter(lfdpr_ctx* ctx, const uint32_t* sub, uint32_t* out) {
 
 int lfdpr_get_stats(lfdpr_ctx* ctx, lfdpr_stats* out) {
   if (!ctx || !out) return fail(ctx, LFDPR_EINVAL, "null argument");
-  uint64_t st[STAT_SLOTS];
+  uint64_t st[kStatWords];
   HIPOK(hipSetDevice(ctx->device));
   HIPOK(sync_all(ctx));
   HIPOK(hipMemcpy(st, ctx->d_stats, sizeof st, hipMemcpyDeviceToHost));
+  add_stat_lines(st);
   std::memset(out, 0, sizeof *out);
   out->points = (int64_t)st[STAT_TOTAL];
   out->active_tris = (int64_t)st[STAT_ACTIVE];
@@ -1559,11 +1570,12 @@ hipEvent_t batch_gen(lfdpr_batch* b, hipStream_t st, bool timed) {
   sa.stats = b->stats;
   sa.tm = pbr ? b->tm : nullptr;
   sa.tile_sum = b->tiles;
+  sa.tile_stat = b->tiles + tile_sum_len(b->nt);
   sa.big = b->big;
   sa.n_big = b->stats + STAT_BIG;
   launch_tri_setup(sa, st);
   hipEvent_t e1 = ev();
-  launch_scan(b->tiles, b->nt, b->stats + STAT_TOTAL, st);
+  launch_scan(sa.tile_sum, sa.tile_stat, b->nt, b->stats, st);
   hipEvent_t e2 = ev();
   EmitArgs ea{};
   ea.items = b->d_items;
@@ -1776,7 +1788,7 @@ int lfdpr_batch_create(lfdpr_ctx* ctx, int32_t n, const int32_t* scene_ids, cons
   if (ok)
     ok = dalloc(b->keys, (size_t)(b->per_item_px * n)) == hipSuccess && dalloc(b->counts, ntb) == hipSuccess &&
          dalloc(b->offsets, ntb) == hipSuccess && dalloc(b->rec, ntb) == hipSuccess && dalloc(b->em, ntb) == hipSuccess &&
-         dalloc(b->tiles, tile_sum_len(ntb)) == hipSuccess && dalloc(b->big, ntb) == hipSuccess &&
+         dalloc(b->tiles, 2 * tile_sum_len(ntb)) == hipSuccess && dalloc(b->big, ntb) == hipSuccess &&
          dalloc(b->tris, ntb) == hipSuccess && dalloc(b->rows, (size_t)b->cap) == hipSuccess &&
          dalloc(b->pbox, (size_t)b->cap) == hipSuccess &&
          dalloc(b->stats, kStatWords) == hipSuccess && dalloc(b->points, (size_t)b->cap) == hipSuccess &&
@@ -1849,7 +1861,7 @@ int lfdpr_batch_set_frames_in_flight(lfdpr_batch* b, int32_t n) {
          hipEventCreateWithFlags(&b->ev_spl[k], hipEventDisableTiming) == hipSuccess;
   if (ok)
     ok = dalloc(a.counts, ntb) == hipSuccess && dalloc(a.offsets, ntb) == hipSuccess && dalloc(a.rec, ntb) == hipSuccess &&
-         dalloc(a.em, ntb) == hipSuccess && dalloc(a.tiles, tile_sum_len(ntb)) == hipSuccess &&
+         dalloc(a.em, ntb) == hipSuccess && dalloc(a.tiles, 2 * tile_sum_len(ntb)) == hipSuccess &&
          dalloc(a.big, ntb) == hipSuccess && dalloc(a.stats, kStatWords) == hipSuccess &&
          dalloc(a.tris, ntb) == hipSuccess && dalloc(a.rows, (size_t)b->cap) == hipSuccess &&
          dalloc(a.pbox, (size_t)b->cap) == hipSuccess &&
@@ -1982,10 +1994,11 @@ int lfdpr_batch_render(lfdpr_batch* b, const float* models, uint32_t* views, uin
 
 int lfdpr_batch_stats(lfdpr_batch* b, lfdpr_stats* out) {
   if (!b || !out) return LFDPR_EINVAL;
-  uint64_t st[STAT_SLOTS];
+  uint64_t st[kStatWords];
   BHIP(hipSetDevice(b->ctx->device));
   BHIP(hipStreamSynchronize(b->stream));
   BHIP(hipMemcpy(st, b->stats, sizeof st, hipMemcpyDeviceToHost));
+  add_stat_lines(st);
   std::memset(out, 0, sizeof *out);
   out->points = (int64_t)st[STAT_TOTAL];
   out->active_tris = (int64_t)st[STAT_ACTIVE];

@@ -10,11 +10,15 @@ namespace lfdpr {
 enum StatSlot { STAT_ACTIVE = 0, STAT_OVERFLOW = 1, STAT_POINT_VIEWS = 2, STAT_TOTAL = 3, STAT_BIG = 4,
                 STAT_WRITTEN = 5, STAT_EMITTING = 6, STAT_COVERED = 7, STAT_SLOTS = 8 };
 
-// The statistics buffer also holds the counters of the point splat's work
-// queues, a 128-byte line each, cleared with them at the start of a frame.
+// The statistics buffer continues with 64 lines of 128 bytes, cleared with it at
+// the start of a frame: the counter of a work queue of the point splat, and
+// shares of STAT_WRITTEN and STAT_COVERED.  (One address takes some 60 to 150
+// atomics in a microsecond: thousands of waves adding to one counter are a
+// launch's length by themselves.)
 constexpr int kWorkQueues = 64;
-constexpr int kWorkNext = 16;  // 64-bit words before the first counter
-constexpr int64_t kStatWords = kWorkNext + 16 * kWorkQueues;
+constexpr int kStatLines = 16;  // 64-bit words before the first line
+enum LineSlot { LINE_NEXT = 0, LINE_WRITTEN = 1, LINE_COVERED = 2, LINE_WORDS = 16 };
+constexpr int64_t kStatWords = kStatLines + LINE_WORDS * kWorkQueues;
 
 // One frame of one scene inside a (possibly single-element) batch.  Items share
 // the view size and projection (W, H, fovy, aspect); eye tables may differ.
@@ -57,6 +61,7 @@ struct SetupArgs {
   uint64_t* stats;
   TriMat* tm;      // physically based mode: per-triangle material records; else null
   uint64_t* tile_sum;  // per workgroup (256 / setup_lanes(nt) triangles): the sum of their counts
+  uint64_t* tile_stat; // and their statistics: point-views | active << 36 | overflowed << 50
   uint32_t* big;       // triangles with more than kBigCells cells (capacity nt)
   uint64_t* n_big;     // and their number
 };
@@ -169,10 +174,11 @@ void launch_export_stats(const uint64_t* st, int64_t cap, int64_t* out, hipStrea
 void launch_build_mip(const uint32_t* src, uint32_t* dst, int s, hipStream_t st);
 // Lanes of the set-up per triangle, and entries of tile_sum for nt triangles.
 int setup_lanes(int64_t nt);
-constexpr int64_t tile_sum_len(int64_t nt) { return (nt + 31) / 32 + 1; }
+constexpr int64_t tile_sum_len(int64_t nt) { return (nt + 31) / 32 + 1; }  // of tile_stat too
 void launch_tri_setup(const SetupArgs& a, hipStream_t s);
-// tile sums (written by the set-up) -> exclusive tile bases, and the total
-void launch_scan(uint64_t* tile_sum, int64_t nt, uint64_t* total, hipStream_t s);
+// tile sums (written by the set-up) -> exclusive tile bases, and the frame's
+// totals in stats
+void launch_scan(uint64_t* tile_sum, const uint64_t* tile_stat, int64_t nt, uint64_t* stats, hipStream_t s);
 void launch_emit(const EmitArgs& a, int fetch_blocks, hipStream_t s);
 void launch_splat(const SplatArgs& a, int grid_blocks, hipStream_t s);
 // the quilt: band lists (bins), then one workgroup per (band, view subset)
