@@ -473,7 +473,6 @@ __global__ void __launch_bounds__(256) k_tri_setup(SetupArgs a) {
 // adds the prefix within its tile of 256 triangles (one or eight workgroups of
 // the set-up).
 
-constexpr int kScanTile = 256;  // triangles per emission workgroup
 
 __global__ void __launch_bounds__(1024) k_scan_top(uint64_t* __restrict__ tile_sum,
                                                     const uint64_t* __restrict__ tile_stat, int64_t ntiles,
@@ -544,8 +543,10 @@ __device__ __forceinline__ void write_head(Point* pts, uint64_t gi, uint32_t t, 
 // spread over the lanes; rows follow each other in emission order, so a scan of
 // their cells places them.  Against a lane per triangle (up to 96 cells in one
 // lane): 1.0M triangles 95 -> 77 us, 0.18M 62 -> 34 us.
+constexpr int kEmitTile = 256;  // triangles per workgroup of a large scene
 constexpr unsigned kEmitBigBlocks = 1024;
 
+template <int kTile>
 __device__ __forceinline__ void emit_big(const EmitArgs& a, uint64_t* ws4) {
   const uint64_t nbig = *a.n_big;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -553,13 +554,13 @@ __device__ __forceinline__ void emit_big(const EmitArgs& a, uint64_t* ws4) {
     const uint32_t t = a.big[b];
     const TriEmit& E = a.em[t];
     // the triangle's first point: the tile base plus the earlier counts in the tile
-    const int64_t t0 = (int64_t)t - (int64_t)t % kScanTile;
+    const int64_t t0 = (int64_t)t - (int64_t)t % kTile;
     const int64_t u = t0 + threadIdx.x;
     const uint64_t cu = u < (int64_t)t ? a.counts[u] : 0u;
     uint64_t wsum = wave_sum(cu);
     if (lane == 0) ws4[wv] = wsum;
     __syncthreads();
-    const uint64_t base = a.tile_base[t0 / kScanTile * a.tile_step] + (ws4[0] + ws4[1]) + (ws4[2] + ws4[3]);
+    const uint64_t base = a.tile_base[t0 / kTile * a.tile_step] + (ws4[0] + ws4[1]) + (ws4[2] + ws4[3]);
     __syncthreads();
     Lattice L;
     lattice_init(L, E.s1, E.t1, E.s2, E.t2);
@@ -594,23 +595,25 @@ __device__ __forceinline__ void emit_big(const EmitArgs& a, uint64_t* ws4) {
   }
 }
 
+template <int kTile>
 __global__ void __launch_bounds__(256) k_emit(EmitArgs a) {
   __shared__ uint64_t ws4[4];
   if (blockIdx.x < kEmitBigBlocks) {
-    emit_big(a, ws4);
+    emit_big<kTile>(a, ws4);
     return;
   }
-  __shared__ int4 l_st[kScanTile];         // s1, t1, s2, t2
-  __shared__ int32_t l_jlo[kScanTile], l_jhi[kScanTile];
-  __shared__ uint32_t l_rows[kScanTile];   // rows of the small triangles before this one
-  __shared__ uint32_t l_first[kScanTile];  // its first point in the tile, and
-  __shared__ uint32_t l_skip[kScanTile];   // the points of big triangles before it
+  __shared__ int4 l_st[kTile];         // s1, t1, s2, t2
+  __shared__ int32_t l_jlo[kTile], l_jhi[kTile];
+  __shared__ uint32_t l_rows[kTile];   // rows of the small triangles before this one
+  __shared__ uint32_t l_first[kTile];  // its first point in the tile, and
+  __shared__ uint32_t l_skip[kTile];   // the points of big triangles before it
   const int64_t tile = (int64_t)blockIdx.x - kEmitBigBlocks;
-  const int64_t t0 = tile * kScanTile, t = t0 + threadIdx.x;
-  const uint32_t cnt = t < a.nt ? a.counts[t] : 0u;
+  const int64_t t0 = tile * kTile, t = t0 + threadIdx.x;
+  const bool mine = (kTile == 256 || threadIdx.x < kTile) && t < a.nt;
+  const uint32_t cnt = mine ? a.counts[t] : 0u;
   const uint64_t tbase = a.tile_base[tile * a.tile_step];
   const uint32_t first = (uint32_t)block_excl_scan(cnt, ws4);  // 256 triangles of at most kCellCap points
-  if (t < a.nt) a.offsets[t] = tbase + first;
+  if (mine) a.offsets[t] = tbase + first;
   if (a.tris) {
     const uint64_t slot = wave_append(cnt > 0, a.n_tris);
     if (cnt > 0) a.tris[slot] = (uint32_t)t;
@@ -626,16 +629,18 @@ __global__ void __launch_bounds__(256) k_emit(EmitArgs a) {
   }
   // one scan for both: rows (high word) and points of the big triangles (low word)
   const uint64_t sc = block_excl_scan(((uint64_t)nrows << 32) | (cnt > kBigCells ? cnt : 0u), ws4);
-  l_rows[threadIdx.x] = (uint32_t)(sc >> 32);
-  l_skip[threadIdx.x] = (uint32_t)sc;
-  l_first[threadIdx.x] = first;
+  if (kTile == 256 || threadIdx.x < kTile) {
+    l_rows[threadIdx.x] = (uint32_t)(sc >> 32);
+    l_skip[threadIdx.x] = (uint32_t)sc;
+    l_first[threadIdx.x] = first;
+  }
   const uint32_t total = (uint32_t)block_sum(nrows, ws4);
   uint32_t run = 0;  // points of the rows of earlier passes
   for (uint32_t k0 = 0; k0 < total; k0 += 256) {
     const uint32_t k = k0 + threadIdx.x;
     int q = 0;  // the last triangle whose rows begin at or before k: it has some
 #pragma unroll
-    for (int st = kScanTile / 2; st >= 1; st >>= 1)
+    for (int st = kTile / 2; st >= 1; st >>= 1)
       if (l_rows[q + st] <= k) q += st;
     int64_t j = 0, lo = 1, hi = 0;
     if (k < total) {
@@ -2083,8 +2088,12 @@ void launch_scan(uint64_t* tile_sum, const uint64_t* tile_stat, int64_t nt, uint
 void launch_emit(const EmitArgs& args, int fetch_blocks, hipStream_t s) {
   if (args.nt <= 0) return;
   EmitArgs a = args;
-  a.tile_step = kScanTile * setup_lanes(a.nt) / 256;
-  k_emit<<<kEmitBigBlocks + nblk(a.nt, kScanTile), 256, 0, s>>>(a);
+  // tiles of 32 triangles spread the rows of a small scene over more workgroups
+  const int tile = a.nt < kSplitTris ? 32 : kEmitTile;
+  a.tile_step = tile * setup_lanes(a.nt) / 256;
+  const unsigned g = kEmitBigBlocks + nblk(a.nt, tile);
+  if (tile == 32) k_emit<32><<<g, 256, 0, s>>>(a);
+  else k_emit<kEmitTile><<<g, 256, 0, s>>>(a);
   if (a.pbox && a.tm)
     k_fetch<true, true><<<fetch_blocks, 256, 0, s>>>(a);
   else if (a.pbox)
