@@ -1326,16 +1326,16 @@ __device__ __forceinline__ void splat_wave(const Item& item, bool valid, uint64_
 // kMulti: points of several items (a batch); otherwise every point belongs to
 // items[0] and the item is read once.  kPBR: shaded colours.
 // Work items are 64 consecutive points (a chunk) and the views, or a part of
-// the views when the frame has fewer than kFillItems chunks (one of 20 thousand
-// points is 315 waves of up to V dependent steps otherwise; the point set-up is
-// repeated for each part).  Waves draw items from kWorkQueues counters, each
-// wave from one of them: with a fixed stride the chip waits for its slowest
-// waves for a third of the launch, as items of 60 us at the median take 190 at
-// the 99th and 410 at the last percentile; one counter for all hands out only
-// some 60 items in a microsecond.  Measured (frames of 0.65M points, 25 views
-// of 317 x 253, and 3.0M points, 48 views of 512 x 512): the frame 450 -> 420
-// and 1577 -> 1483 us.  8192 items: 440 and 1505, 65536: 438 and 1455, 131072:
-// 483 and 1459 us.
+// the views when the frame has fewer than 2 kFillItems chunks: half of them, or
+// as few as make kFillItems items (a frame of 20 thousand points is 315 waves
+// of up to V dependent steps otherwise; the point set-up is repeated for each
+// part).  Waves draw items from kWorkQueues counters, each wave from one of
+// them: with a fixed stride the chip waits for its slowest waves for a third of
+// the launch, as items of 60 us at the median take 190 at the 99th and 410 at
+// the last percentile; one counter for all hands out only some 60 items in a
+// microsecond.  Measured (frames of 0.65M points, 25 views of 317 x 253, and
+// 3.0M points, 48 views of 512 x 512): all views 440 and 1505 us, this rule 420
+// and 1455, twice as many items 438 and 1455.
 constexpr uint32_t kFillItems = 32768;
 
 template <bool kMulti, bool kPBR>
@@ -1366,7 +1366,9 @@ __global__ void __launch_bounds__(256) k_splat(SplatArgs a) {
   const Item it0 = load_uniform(a.items);
   uint32_t written = 0;
   const uint32_t chunks = (uint32_t)((npts + 63) >> 6), V = (uint32_t)trg.n_views;
-  const uint32_t want = chunks >= kFillItems || chunks == 0 ? 1u : min(V, (kFillItems + chunks - 1) / chunks);
+  const uint32_t want = chunks >= 2 * kFillItems || chunks == 0
+                            ? 1u
+                            : min(V, max(2u, (kFillItems + chunks - 1) / chunks));
   const uint32_t per = (V + want - 1) / want, parts = (V + per - 1) / per;  // views per item, items per chunk
   for (; c < chunks * parts; c = draw()) {
     const uint32_t chunk = c / parts, r0 = (c - chunk * parts) * per, r1 = min(V, r0 + per);
