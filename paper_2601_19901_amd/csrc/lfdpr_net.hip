@@ -24,6 +24,7 @@
 // same order, so the K ordering inside a group does not matter.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -379,170 +380,178 @@ __global__ void __launch_bounds__(256) k_conv3x3(const uint16_t* __restrict__ X,
 }
 
 // ---------------------------------------------------------------- weight gradient
-// dW[tap][co][ci] = sum_p dZ[p][co] * A[p + off(tap)][ci].  A block owns a
-// chunk of pixels; 256 of them at a time it stages dZ, and for each tap the
-// shifted activations, in LDS channel-major (rows of 256 pixels padded by 16
-// bytes, so the 8 lanes of a 128-byte read group hit distinct banks); wave w
-// then reduces its (co tile w/2, ci tile w%2) over the pixels with one MFMA
-// per 32 pixels (M = co, N = ci, K = pixels).  Each block writes its sums to
-// its own row of a partials buffer, which k_sum_partials adds in block order.
-constexpr int kWgPix = 256;
-constexpr int kMaxGradBlocks = 1024;  // blocks of one gradient sum (partials buffer rows)
-constexpr int kWgPitch = kWgPix + 8;  // bf16 per LDS row
+// dW[tap][co][ci] = sum_p dZ[p][co] * A[p + off(tap)][ci], db[co] = sum_p dZ[p][co].
+//
+// The contraction runs over pixels, so both operands need eight pixels of one
+// channel in a lane while memory holds 32 channels of one pixel: the tile is
+// staged as it lies (dZ of kGY x kGX pixels, A with the taps' halo, loaded once
+// for all nine taps) and read through the transposing LDS loads, four pixels x
+// 16 channels per 16 lanes.  Wave w of three takes the taps of row w - 1: per 16
+// pixels one dZ operand and, for each tap, the shifted A operand and one
+// v_mfma_f32_32x32x16_bf16 over all 32 x 32 channels; no sums cross waves.  The
+// next tile is fetched into registers meanwhile.  (Four waves with a row of the
+// tile each and all nine taps: 60 us, most of it adding up the waves' sums.  Staging each tap's shifted pixels channel by channel
+// through two-byte LDS writes instead: 48 x 128 x 128 pixels, 60-72 -> 30-39 us a
+// layer, and 9 us for the biases.)
+//
+// Workgroups take tiles grid, 2 grid, .. apart and write their sums to their own
+// row of a partials buffer laid out as the parameter vector, which
+// k_sum_partials adds in row order: gradients come out the same on every run.
+constexpr int kGX = 64, kGY = 4, kGThreads = 192;
+constexpr int kGradBlocks = 512;  // rows of the partials buffer: two workgroups per CU
+typedef short i16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-__device__ __forceinline__ void put_cols(uint16_t* T, int col, const uint4 (&v)[4]) {
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const uint32_t w[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
-#pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      T[(8 * q + 2 * h) * kWgPitch + col] = (uint16_t)(w[h] & 0xFFFFu);
-      T[(8 * q + 2 * h + 1) * kWgPitch + col] = (uint16_t)(w[h] >> 16);
-    }
-  }
+// Eight pixels (p0 .. p0+3 and p0+4 .. p0+7 of this lane's half, in tile order)
+// of channel lane % 32 from rows of 32 channels; `at` is this lane's address in
+// the first read: pixel (lane >> 2) & 3 of its half, channels 16 ((lane >> 4) & 1)
+// + 4 (lane & 3).
+__device__ __forceinline__ bf16x8 read_pixels(const uint16_t* at) {
+  typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
+  union {
+    i16x4 q[2];
+    bf16x8 v;
+  } f;
+  f.q[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)at);
+  f.q[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(at + 4 * kK));
+  return f.v;
 }
 
-template <bool GATHER>
-__global__ void __launch_bounds__(256) k_conv_wgrad(const uint16_t* __restrict__ dZ, int CO,
+template <bool GATHER, int DIL>
+__global__ void __launch_bounds__(kGThreads) k_conv_wgrad(const uint16_t* __restrict__ dZ, int CO,
                                                      const uint16_t* __restrict__ A, const uint16_t* __restrict__ AB,
-                                                     int CI, int N, int H, int W, int V, int DIL,
-                                                     float* __restrict__ dW, int chunk) {
-  __shared__ uint16_t dzT[kK * kWgPitch];
-  __shared__ uint16_t aT[kK * kWgPitch];
+                                                     int CI, int N, int H, int W, int V, float* __restrict__ part,
+                                                     int part_row) {
+  constexpr int TW = kGX + 2 * DIL, kAPix = (kGY + 2) * TW, kZPix = kGY * kGX;
+  constexpr int kAItems = (kAPix * 4 + kGThreads - 1) / kGThreads, kZItems = (kZPix * 4 + kGThreads - 1) / kGThreads;
+  static_assert(kGThreads % 4 == 0, "a thread stages one 16-byte group of its pixels");
+  __shared__ __attribute__((aligned(16))) uint16_t at[kAPix * kK], zt[kZPix * kK];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int g = lane >> 4, r16 = lane & 15;
-  const int ct = wv >> 1, it = wv & 1;
-  const bool active = ct * 16 < CO && it * 16 < CI;  // wave-uniform
-  const int hw = H * W, npx = N * hw;
-  const int c0 = blockIdx.x * chunk, c1 = min(npx, c0 + chunk);
-  f32x4 acc[9];
+  const int tiles_x = (W + kGX - 1) / kGX, tiles_y = (H + kGY - 1) / kGY, ntile = N * tiles_x * tiles_y;
+  const int sg = threadIdx.x & 3;
+  uint4 pa[kAItems], pz[kZItems];
+  auto fetch = [&](int tile) {
+    const int n = tile / (tiles_x * tiles_y), pos = tile % (tiles_x * tiles_y);
+    const int y0 = pos / tiles_x * kGY, x0 = pos % tiles_x * kGX;
 #pragma unroll
-  for (int k = 0; k < 9; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int base = c0; base < c1; base += kWgPix) {
-    const int p = base + (int)threadIdx.x;
-    const bool pv = p < c1;
-    const int n = pv ? p / hw : 0, q = pv ? p % hw : 0;
-    const int y = q / W, x = q % W;
-    __syncthreads();  // the previous chunk's reads are done
-    {
-      uint4 v[4] = {};
-      if (pv) {
-#pragma unroll
-        for (int c4 = 0; c4 < 4; ++c4) v[c4] = reinterpret_cast<const uint4*>(dZ + (size_t)p * kK)[c4];
-      }
-      put_cols(dzT, threadIdx.x, v);
+    for (int j = 0; j < kZItems; ++j) {
+      const int q = (int)(threadIdx.x >> 2) + kGThreads / 4 * j, y = y0 + q / kGX, x = x0 + q % kGX;
+      pz[j] = q < kZPix && y < H && x < W ? *reinterpret_cast<const uint4*>(dZ + (size_t)((n * H + y) * W + x) * kK + 8 * sg)
+                                          : uint4{0u, 0u, 0u, 0u};
     }
 #pragma unroll
-    for (int tap = 0; tap < 9; ++tap) {  // unrolled: acc[tap] stays in registers
-      const int yy = y + tap / 3 - 1, xx = x + (tap % 3 - 1) * DIL;
-      uint4 v[4] = {};
-      if (pv) {
+    for (int j = 0; j < kAItems; ++j) {
+      const int q = (int)(threadIdx.x >> 2) + kGThreads / 4 * j;
+      pa[j] = q < kAPix ? load_a<GATHER>(A, AB, n, y0 - 1 + q / TW, x0 - DIL + q % TW, H, W, sg, V) : uint4{0u, 0u, 0u, 0u};
+    }
+  };
+  f32x16 acc[3];
 #pragma unroll
-        for (int c4 = 0; c4 < 4; ++c4) v[c4] = load_a<GATHER>(A, AB, n, yy, xx, H, W, c4, V);
-      }
-      __syncthreads();  // the previous tap's reads of aT are done
-      put_cols(aT, threadIdx.x, v);
-      __syncthreads();
-      if (active) {
+  for (int k = 0; k < 3; ++k)
 #pragma unroll
-        for (int k = 0; k < kWgPix / 32; ++k) {
-          Frag fa, fb;
-          fa.u = *reinterpret_cast<const uint4*>(&dzT[(ct * 16 + r16) * kWgPitch + k * 32 + 8 * g]);
-          fb.u = *reinterpret_cast<const uint4*>(&aT[(it * 16 + r16) * kWgPitch + k * 32 + 8 * g]);
-          acc[tap] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa.v, fb.v, acc[tap], 0, 0, 0);
+    for (int e = 0; e < 16; ++e) acc[k][e] = 0.f;
+  float bsum = 0.f;  // wave 0: dZ of channel lane % 32, this half's pixels
+  const int px = 8 * (lane >> 5) + ((lane >> 2) & 3), ch = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+  fetch(blockIdx.x);
+  for (int tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
+    __syncthreads();  // the previous tile's reads are done
+#pragma unroll
+    for (int j = 0; j < kZItems; ++j)
+      if ((int)threadIdx.x + kGThreads * j < kZPix * 4) reinterpret_cast<uint4*>(zt)[threadIdx.x + kGThreads * j] = pz[j];
+#pragma unroll
+    for (int j = 0; j < kAItems; ++j)
+      if ((int)threadIdx.x + kGThreads * j < kAPix * 4) reinterpret_cast<uint4*>(at)[threadIdx.x + kGThreads * j] = pa[j];
+    __syncthreads();
+    if (tile + (int)gridDim.x < ntile) fetch(tile + gridDim.x);
+#pragma unroll
+    for (int row = 0; row < kGY; ++row)
+#pragma unroll
+      for (int k = 0; k < kGX / 16; ++k) {
+        const bf16x8 fz = read_pixels(zt + (row * kGX + 16 * k + px) * kK + ch);
+        if (wv == 0)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) bsum += (float)fz[e];
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+          const bf16x8 fa = read_pixels(at + ((row + wv) * TW + 16 * k + t * DIL + px) * kK + ch);
+          acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fz, fa, acc[t], 0, 0, 0);
         }
       }
+  }
+  // lane holds D[8 (e / 4) + 4 (lane / 32) + e % 4][lane % 32]
+  float* const out = part + (size_t)blockIdx.x * part_row;
+  const int ci = lane & 31;
+#pragma unroll
+  for (int t = 0; t < 3; ++t)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int co = 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+      if (co < CO && ci < CI) out[((3 * wv + t) * CO + co) * CI + ci] = acc[t][e];
     }
-  }
-  // lane holds D[4g+e][r16]: co = ct*16 + 4g + e, ci = it*16 + r16
-  if (active) {
-    const int ci = it * 16 + r16;
-#pragma unroll
-    for (int tap = 0; tap < 9; ++tap)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int co = ct * 16 + 4 * g + e;
-        if (co < CO && ci < CI) dW[(size_t)blockIdx.x * 9 * CO * CI + ((size_t)tap * CO + co) * CI + ci] = acc[tap][e];
-      }
-  }
+  bsum += __shfl_xor(bsum, 32, 64);
+  if (wv == 0 && lane < CO && lane < 32) out[9 * CO * CI + lane] = bsum;
 }
 
-__global__ void __launch_bounds__(256) k_bias_grad(const uint16_t* __restrict__ dZ, int CO, int npx, int chunk,
-                                                    float* __restrict__ db) {
-  // db[block][c] = sum over the block's pixels of dZ[p][c] (dZ [p][32] BF16):
-  // thread t adds channels 8(t % 4) .. +7 of pixels t / 4, t / 4 + 64, .. from
-  // 16-byte loads; the 64 partial sums of each channel meet in LDS
-  __shared__ float red[8][256];
-  const int g = threadIdx.x & 3, q = threadIdx.x >> 2;
-  const int p0 = blockIdx.x * chunk, p1 = min(npx, p0 + chunk);
-  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  for (int p = p0 + q; p < p1; p += 64) {
-    const uint4 v = *reinterpret_cast<const uint4*>(dZ + (size_t)p * kK + 8 * g);
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      acc[2 * h] += from_bf16((uint16_t)(w[h] & 0xFFFFu));
-      acc[2 * h + 1] += from_bf16((uint16_t)(w[h] >> 16));
-    }
-  }
-#pragma unroll
-  for (int e = 0; e < 8; ++e) red[e][threadIdx.x] = acc[e];
-  __syncthreads();
-  if ((int)threadIdx.x < CO) {
-    const int c = threadIdx.x, gg = c >> 3, e = c & 7;
-    float sum = 0.0f;
-    for (int k = 0; k < 64; ++k) sum += red[e][gg + 4 * k];
-    db[(size_t)blockIdx.x * CO + c] = sum;
-  }
-}
-
-// out[i] = sum over the nblk rows of part[b][i] in a fixed order, so gradients
-// come out the same on every run (no atomics in their sums): in a block of 256,
-// lane (phase f = t / 16, column j = t % 16) adds rows f, f + 16, .. in
-// ascending order, then the 16 phase sums of each column are added in phase
-// order.  Grid: ceil(n / 16) blocks.
+// out[i] = sum over the nblk rows of part[b][i] in a fixed order: in a block of
+// 256, lane (phase f = t / 32, column j = t % 32) adds rows f, f + 8, .. in
+// ascending order, then the 8 phase sums of each column are added in phase
+// order.  The last workgroup adds the loss's nloss partial sums the same way and
+// writes it to *loss0 and, if given, *loss1.  Grid: ceil(n / 32) + 1 blocks.
 __global__ void __launch_bounds__(256) k_sum_partials(const float* __restrict__ part, int nblk, int n,
-                                                       float* __restrict__ out) {
-  __shared__ float red[16][17];
-  const int j = threadIdx.x & 15, f = threadIdx.x >> 4;
-  const int i = blockIdx.x * 16 + j;
+                                                       float* __restrict__ out, const float* __restrict__ loss_part,
+                                                       int nloss, float* __restrict__ loss0, float* __restrict__ loss1) {
+  __shared__ float red[8][32];
+  const int j = threadIdx.x & 31, f = threadIdx.x >> 5;
+  const bool last = blockIdx.x == gridDim.x - 1;
+  const int i = blockIdx.x * 32 + j;
   float sum = 0.0f;
-  if (i < n) {
-#pragma unroll 8
-    for (int b = f; b < nblk; b += 16) sum += part[(size_t)b * n + i];
+  if (last) {
+    for (int b = threadIdx.x; b < nloss; b += 256) sum += loss_part[b];
+  } else if (i < n) {
+#pragma unroll 16
+    for (int b = f; b < nblk; b += 8) sum += part[(size_t)b * n + i];
   }
   red[f][j] = sum;
   __syncthreads();
-  if (f == 0 && i < n) {
+  if (last) {
+    if (threadIdx.x == 0) {
+      float total = 0.0f;
+      for (int k = 0; k < 256; ++k) total += red[k >> 5][k & 31];
+      *loss0 = total;
+      if (loss1) *loss1 = total;
+    }
+  } else if (f == 0 && i < n) {
     float total = 0.0f;
-    for (int k = 0; k < 16; ++k) total += red[k][j];
+    for (int k = 0; k < 8; ++k) total += red[k][j];
     out[i] = total;
   }
 }
 
 // loss = mean((y - t)^2) over the 3 colour channels of npx pixels (inputs
-// [p][4]); dZ = bf16(2 (y - t) / n) into a [p][32] buffer (other channels 0),
-// one pixel (four 16-byte stores) per thread.  Grid-stride, one loss atomic per
-// block.
+// [p][4]), as one partial sum per workgroup; dZ = bf16(2 (y - t) / n) into a
+// [p][32] buffer (other channels 0).  Four lanes per pixel, one 16-byte store
+// each, so that a wave writes 1 KiB in a row.
+constexpr int kMseBlocks = 2048;
 __global__ void __launch_bounds__(256) k_mse(const uint16_t* __restrict__ Yb, const uint16_t* __restrict__ T, int npx,
-                                              uint16_t* __restrict__ dZ, float* __restrict__ loss) {
+                                              uint16_t* __restrict__ dZ, float* __restrict__ loss_part) {
   const int64_t n = (int64_t)npx * 3;
   float sq = 0.0f;
-  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < npx; p += (int64_t)gridDim.x * blockDim.x) {
-    const uint2 yv = *reinterpret_cast<const uint2*>(Yb + p * 4);
-    const uint2 tv = *reinterpret_cast<const uint2*>(T + p * 4);
-    const float d0 = from_bf16((uint16_t)(yv.x & 0xFFFFu)) - from_bf16((uint16_t)(tv.x & 0xFFFFu));
-    const float d1 = from_bf16((uint16_t)(yv.x >> 16)) - from_bf16((uint16_t)(tv.x >> 16));
-    const float d2 = from_bf16((uint16_t)(yv.y & 0xFFFFu)) - from_bf16((uint16_t)(tv.y & 0xFFFFu));
-    sq += d0 * d0;
-    sq += d1 * d1;
-    sq += d2 * d2;
-    uint4* out = reinterpret_cast<uint4*>(dZ + p * kK);
-    out[0] = uint4{(uint32_t)to_bf16((2.0f * d0) / (float)n) | ((uint32_t)to_bf16((2.0f * d1) / (float)n) << 16),
-                   (uint32_t)to_bf16((2.0f * d2) / (float)n), 0u, 0u};
-    out[1] = uint4{0u, 0u, 0u, 0u};
-    out[2] = uint4{0u, 0u, 0u, 0u};
-    out[3] = uint4{0u, 0u, 0u, 0u};
+  const int g = threadIdx.x & 3;
+  for (int64_t p = (int64_t)blockIdx.x * 64 + (threadIdx.x >> 2); p < npx; p += (int64_t)gridDim.x * 64) {
+    uint4 o{0u, 0u, 0u, 0u};
+    if (g == 0) {
+      const uint2 yv = *reinterpret_cast<const uint2*>(Yb + p * 4);
+      const uint2 tv = *reinterpret_cast<const uint2*>(T + p * 4);
+      const float d0 = from_bf16((uint16_t)(yv.x & 0xFFFFu)) - from_bf16((uint16_t)(tv.x & 0xFFFFu));
+      const float d1 = from_bf16((uint16_t)(yv.x >> 16)) - from_bf16((uint16_t)(tv.x >> 16));
+      const float d2 = from_bf16((uint16_t)(yv.y & 0xFFFFu)) - from_bf16((uint16_t)(tv.y & 0xFFFFu));
+      sq += d0 * d0;
+      sq += d1 * d1;
+      sq += d2 * d2;
+      o.x = (uint32_t)to_bf16((2.0f * d0) / (float)n) | ((uint32_t)to_bf16((2.0f * d1) / (float)n) << 16);
+      o.y = (uint32_t)to_bf16((2.0f * d2) / (float)n);
+    }
+    reinterpret_cast<uint4*>(dZ + p * kK)[g] = o;
   }
   __shared__ float red[256];
   red[threadIdx.x] = sq;
@@ -551,7 +560,7 @@ __global__ void __launch_bounds__(256) k_mse(const uint16_t* __restrict__ Yb, co
     if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
     __syncthreads();
   }
-  if (threadIdx.x == 0 && loss) atomicAdd(loss, red[0] / (float)n);
+  if (threadIdx.x == 0) loss_part[blockIdx.x] = red[0] / (float)n;
 }
 
 __global__ void k_adam(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m, float* __restrict__ v,
@@ -681,11 +690,6 @@ __global__ void k_unpack_output(const uint16_t* __restrict__ y, int64_t n, uint3
   views[i] = o;
 }
 
-__global__ void k_zero_f32(float* p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0.0f;
-}
-
 }  // namespace net
 }  // namespace lfdpr
 
@@ -717,7 +721,7 @@ struct lfdpr_net {
   const uint16_t* last_y = nullptr;
   int last_n = 0, last_h = 0, last_w = 0;
   float* d_loss = nullptr;
-  float* part = nullptr;   // per-block partial gradients: kMaxGradBlocks x (9*32*32 + 32)
+  float* part = nullptr;   // per-block partial gradients (kGradBlocks rows of nparams), then kMseBlocks of the loss
   std::string err;
 };
 
@@ -783,7 +787,7 @@ int lfdpr_net_create(lfdpr_ctx* ctx, int32_t V, int32_t max_h, int32_t max_w, lf
   al(net->adam_m, off);
   al(net->adam_v, off);
   al(net->d_loss, 1);
-  al(net->part, (size_t)kMaxGradBlocks * (9 * kHidden * kHidden + kHidden));
+  al(net->part, (size_t)kGradBlocks * off + kMseBlocks);
   for (int k = 0; k < 4; ++k) {
     al(net->wf[k], 9ll * net->cof[k] * kK);
     if (k > 0) al(net->wb[k], 9ll * ci[k] * kK);
@@ -936,37 +940,29 @@ int lfdpr_net_backward(lfdpr_net* net, const void* target, float* loss) {
   hipStream_t s = net->stream;
   const int N = net->last_n, H = net->last_h, W = net->last_w, V = net->V;
   const int npx = N * H * W;
-  k_zero_f32<<<(unsigned)((net->nparams + 255) / 256), 256, 0, s>>>(net->grad, net->nparams);
-  k_zero_f32<<<1, 64, 0, s>>>(net->d_loss, 1);
-  const int64_t mse_blocks = ((int64_t)npx + 255) / 256;
-  k_mse<<<(unsigned)(mse_blocks < 2048 ? mse_blocks : 2048), 256, 0, s>>>(net->last_y, (const uint16_t*)target, npx,
-                                                                           net->dz[4], net->d_loss);
-  // Gradient sums: at most kMaxGradBlocks blocks each (multiples of 256 pixels
-  // for the weights, of 64 for the biases), then k_sum_partials in block order.
-  const int chunk = (int)((((int64_t)npx + kMaxGradBlocks - 1) / kMaxGradBlocks + 255) / 256 * 256);
-  const unsigned nch = (unsigned)((npx + chunk - 1) / chunk);
-  const int bchunk = (int)((((int64_t)npx + kMaxGradBlocks - 1) / kMaxGradBlocks + 63) / 64 * 64);
-  const unsigned nbch = (unsigned)((npx + bchunk - 1) / bchunk);
-  float* const part_w = net->part;
-  float* const part_b = net->part + (size_t)kMaxGradBlocks * 9 * kHidden * kHidden;
+  float* const loss_part = net->part + (size_t)kGradBlocks * net->nparams;
+  const int mse_blocks = (int)std::min<int64_t>(((int64_t)npx + 63) / 64, kMseBlocks);
+  k_mse<<<mse_blocks, 256, 0, s>>>(net->last_y, (const uint16_t*)target, npx, net->dz[4], loss_part);
+  const int64_t tiles = (int64_t)N * ((H + kGY - 1) / kGY) * ((W + kGX - 1) / kGX);
+  const int rows = (int)std::min<int64_t>(tiles, kGradBlocks);
   for (int k = 3; k >= 0; --k) {
-    const int CO = net->co[k], CI = net->ci[k];
+    const int CO = net->co[k], CI = net->ci[k], np = (int)net->nparams;
+    float* const part = net->part + net->off_w[k];  // the layer's weights, then its biases
     if (k == 0)
-      k_conv_wgrad<true><<<nch, 256, 0, s>>>(net->dz[1], CO, net->last_x, net->xb, CI, N, H, W, V, kDilation[0],
-                                             part_w, chunk);
+      k_conv_wgrad<true, kDilation[0]><<<rows, kGThreads, 0, s>>>(net->dz[1], CO, net->last_x, net->xb, CI, N, H, W, V, part, np);
+    else if (k == 1)
+      k_conv_wgrad<false, kDilation[1]><<<rows, kGThreads, 0, s>>>(net->dz[2], CO, net->act[1], nullptr, CI, N, H, W, V, part, np);
+    else if (k == 2)
+      k_conv_wgrad<false, kDilation[2]><<<rows, kGThreads, 0, s>>>(net->dz[3], CO, net->act[2], nullptr, CI, N, H, W, V, part, np);
     else
-      k_conv_wgrad<false><<<nch, 256, 0, s>>>(net->dz[k + 1], CO, net->act[k], nullptr, CI, N, H, W, V, kDilation[k],
-                                              part_w, chunk);
-    const int nw = 9 * CO * CI;
-    k_sum_partials<<<(unsigned)((nw + 15) / 16), 256, 0, s>>>(part_w, (int)nch, nw, net->grad + net->off_w[k]);
-    k_bias_grad<<<nbch, 256, 0, s>>>(net->dz[k + 1], CO, npx, bchunk, part_b);
-    k_sum_partials<<<(unsigned)((CO + 15) / 16), 256, 0, s>>>(part_b, (int)nbch, CO, net->grad + net->off_b[k]);
+      k_conv_wgrad<false, kDilation[3]><<<rows, kGThreads, 0, s>>>(net->dz[4], CO, net->act[3], nullptr, CI, N, H, W, V, part, np);
     if (k > 0)  // input gradient through the flipped, transposed weights (same dilation), masked by the ReLU
       launch_conv<2, MODE_BWD, false>(net->dz[k + 1], net->wb[k], nullptr, N, H, W, V, kDilation[k], net->dz[k], kHidden,
                                       net->act[k], kHidden, s);
   }
+  k_sum_partials<<<(unsigned)((net->nparams + 31) / 32) + 1, 256, 0, s>>>(net->part, rows, (int)net->nparams, net->grad,
+                                                                          loss_part, mse_blocks, net->d_loss, loss);
   NHIP(hipGetLastError());
-  if (loss) NHIP(hipMemcpyAsync(loss, net->d_loss, 4, hipMemcpyDeviceToDevice, s));
   return LFDPR_OK;
 }
 
