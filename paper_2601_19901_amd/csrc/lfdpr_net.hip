@@ -616,31 +616,33 @@ struct BlurTaps {
   float w[9];
 };
 
-// One output pixel of the blur; px(i) returns input pixel i of the row.
-template <typename RowPx>
-__device__ __forceinline__ uint2 blur_pixel(RowPx px, int x, int W, float k, const BlurTaps& bw) {
-  const float d = from_bf16((uint16_t)(px(x).y >> 16));
+// One output pixel of the blur with the packed disparity word `dw` (d in bits
+// 16-31); pair(i, a, b) sets a, b to the colours of pixels i and i + 1 of the
+// row, i = -1 .. W, indices clamped to the row.
+struct Colour {
+  float r, g, b;
+};
+__device__ __forceinline__ Colour unpack_colour(uint2 c) {
+  return {from_bf16((uint16_t)(c.x & 0xFFFFu)), from_bf16((uint16_t)(c.x >> 16)), from_bf16((uint16_t)(c.y & 0xFFFFu))};
+}
+template <typename Pair>
+__device__ __forceinline__ uint2 blur_pixel(Pair pair, uint32_t dw, int x, int W, float k, const BlurTaps& bw) {
+  const float d = from_bf16((uint16_t)(dw >> 16));
   const float s = d > -1.0f ? k * d : 0.0f;
   float acc[3] = {0.0f, 0.0f, 0.0f};
 #pragma unroll
   for (int j = 0; j < 9; ++j) {
-    const float t = (float)(j - 4) * 0.25f;
-    float u = (float)x + t * s;
-    u = fminf(fmaxf(u, -1.0f), (float)W);
+    const float ts = (j < 4 ? 4 - j : j - 4) * 0.25f * s;
+    float u = j < 4 ? (float)x - ts : (float)x + ts;
+    u = __builtin_amdgcn_fmed3f(u, -1.0f, (float)W);  // a NaN gives -1, as max and min do
     const float fl = floorf(u);
     const float f = u - fl;
-    const int i0 = (int)fl;
-    const int a = min(max(i0, 0), W - 1), b = min(max(i0 + 1, 0), W - 1);
-    const uint2 ca = px(a);
-    const uint2 cb = px(b);
+    Colour a, b;
+    pair((int)fl, a, b);
     const float g = 1.0f - f;
-    const float a0 = from_bf16((uint16_t)(ca.x & 0xFFFFu)), a1 = from_bf16((uint16_t)(ca.x >> 16)),
-                a2 = from_bf16((uint16_t)(ca.y & 0xFFFFu));
-    const float b0 = from_bf16((uint16_t)(cb.x & 0xFFFFu)), b1 = from_bf16((uint16_t)(cb.x >> 16)),
-                b2 = from_bf16((uint16_t)(cb.y & 0xFFFFu));
-    acc[0] = acc[0] + bw.w[j] * (g * a0 + f * b0);
-    acc[1] = acc[1] + bw.w[j] * (g * a1 + f * b1);
-    acc[2] = acc[2] + bw.w[j] * (g * a2 + f * b2);
+    acc[0] = acc[0] + bw.w[j] * (g * a.r + f * b.r);
+    acc[1] = acc[1] + bw.w[j] * (g * a.g + f * b.g);
+    acc[2] = acc[2] + bw.w[j] * (g * a.b + f * b.b);
   }
   uint2 o;
   o.x = pack_bf16x2(acc[0], acc[1]);
@@ -648,21 +650,48 @@ __device__ __forceinline__ uint2 blur_pixel(RowPx px, int x, int W, float k, con
   return o;
 }
 
-// Rows of up to kBlurRowMax pixels: a block stages a whole row (8 bytes per
-// pixel) in LDS with coalesced loads, and every tap is gathered from there.
+// Rows of up to kBlurRowMax pixels: a block stages whole rows in LDS with
+// coalesced loads, and every tap is gathered from there.  Vector instructions
+// bound it (24 a tap, about the same time as the taps' LDS reads), so colours are
+// unpacked once, when staged, and a staged row carries one copy of its first and
+// two of its last pixel: the clamped indices of a tap are then two neighbouring
+// pixels.  Rows are taken in groups of about kBlurGroup pixels, so that few
+// threads of the last pass over a group are idle, as long as kBlurGroups groups
+// are left.  48 x 512 x 512 pixels: 90 us
+// with packed, unpadded rows, 75 now (groups of 512 pixels 78, of 2048 80).
 constexpr int kBlurRowMax = 4096;
+constexpr int kBlurGroup = 1024, kBlurGroups = 1536;
 
-__global__ void __launch_bounds__(256) k_disparity_blur_rows(const uint16_t* __restrict__ X, int64_t nrows, int W,
+inline int blur_rows(int64_t nrows, int W) {
+  return (int)std::max<int64_t>(1, std::min<int64_t>(nrows / kBlurGroups, std::min(64, kBlurGroup / W)));
+}
+
+__global__ void __launch_bounds__(256) k_disparity_blur_rows(const uint16_t* __restrict__ X, int64_t nrows, int W, int R,
                                                               float k, BlurTaps bw, uint16_t* __restrict__ XB) {
-  extern __shared__ uint2 lrow[];  // W pixels
-  for (int64_t r = blockIdx.x; r < nrows; r += gridDim.x) {
-    const uint2* src = reinterpret_cast<const uint2*>(X) + r * W;
-    __syncthreads();  // the previous row's gathers are finished
-    for (int i = threadIdx.x; i < W; i += blockDim.x) lrow[i] = src[i];
+  extern __shared__ Colour lrow[];  // R rows of W + 3 pixels: pixel i at i + 1
+  const int P = W + 3;
+  const int64_t ngroups = (nrows + R - 1) / R;
+  for (int64_t gr = blockIdx.x; gr < ngroups; gr += gridDim.x) {
+    const int64_t r0 = gr * R;
+    const int nr = (int)min((int64_t)R, nrows - r0);
+    const uint2* src = reinterpret_cast<const uint2*>(X) + r0 * W;
+    uint2* dst = reinterpret_cast<uint2*>(XB) + r0 * W;
+    __syncthreads();  // the previous group's gathers are finished
+    for (int i = threadIdx.x, r = i / P, c = i % P; r < nr; i += blockDim.x) {
+      lrow[i] = unpack_colour(src[r * W + min(max(c - 1, 0), W - 1)]);
+      for (c += blockDim.x; c >= P; c -= P) ++r;
+    }
     __syncthreads();
-    uint2* dst = reinterpret_cast<uint2*>(XB) + r * W;
-    for (int x = threadIdx.x; x < W; x += blockDim.x)
-      dst[x] = blur_pixel([&](int i) { return lrow[i]; }, x, W, k, bw);
+    for (int i = threadIdx.x, r = i / W, x = i % W; r < nr; i += blockDim.x) {
+      const Colour* row = lrow + r * P + 1;
+      dst[i] = blur_pixel(
+          [&](int a, Colour& ca, Colour& cb) {
+            ca = row[a];
+            cb = row[a + 1];
+          },
+          src[i].y, x, W, k, bw);
+      for (x += blockDim.x; x >= W; x -= W) ++r;
+    }
   }
 }
 
@@ -673,7 +702,12 @@ __global__ void __launch_bounds__(256) k_disparity_blur(const uint16_t* __restri
   if (p >= npx) return;
   const int x = (int)(p % W);
   const uint2* row = reinterpret_cast<const uint2*>(X) + (p - x);
-  reinterpret_cast<uint2*>(XB)[p] = blur_pixel([&](int i) { return row[i]; }, x, W, k, bw);
+  reinterpret_cast<uint2*>(XB)[p] = blur_pixel(
+      [&](int a, Colour& ca, Colour& cb) {
+        ca = unpack_colour(row[min(max(a, 0), W - 1)]);
+        cb = unpack_colour(row[min(max(a + 1, 0), W - 1)]);
+      },
+      row[x].y, x, W, k, bw);
 }
 
 // y[v][p][4] -> RGBA8, clamp(floor(255 y + 0.5)), alpha 255
@@ -914,9 +948,10 @@ int lfdpr_net_forward(lfdpr_net* net, const void* x, int32_t n_views, int32_t H,
   const int* d = kDilation;
   const int64_t npx = (int64_t)N * H * W;
   if (W <= kBlurRowMax) {
-    const int64_t rows = (int64_t)N * H;
-    k_disparity_blur_rows<<<(unsigned)(rows < 4096 ? rows : 4096), 256, (size_t)W * sizeof(uint2), s>>>(
-        in, rows, W, net->kscale, net->taps, net->xb);
+    const int rows = blur_rows((int64_t)N * H, W);
+    const int64_t groups = ((int64_t)N * H + rows - 1) / rows;
+    k_disparity_blur_rows<<<(unsigned)(groups < 4096 ? groups : 4096), 256, (size_t)rows * (W + 3) * sizeof(Colour), s>>>(
+        in, (int64_t)N * H, W, rows, net->kscale, net->taps, net->xb);
   } else {
     k_disparity_blur<<<(unsigned)((npx + 255) / 256), 256, 0, s>>>(in, npx, W, net->kscale, net->taps, net->xb);
   }
