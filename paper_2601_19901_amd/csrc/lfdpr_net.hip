@@ -29,6 +29,7 @@
 #include <cstdio>
 #include <cstring>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/lfdpr.h"
@@ -96,7 +97,7 @@ __device__ __forceinline__ uint4 load_a(const uint16_t* __restrict__ X, const ui
   return uint4{lo.x, lo.y, hi.x, hi.y};
 }
 
-// One block = 4 waves, persistent over output tiles of kTY rows x kTX pixels of
+// One block = kTY waves, persistent over output tiles of kTY rows x kTX pixels of
 // one image (wave w computes row w: four 16-pixel M tiles); NT = COUT/16
 // output-channel tiles.  All nine taps' [COUT][32] weights stay in LDS; each
 // tile's input, rows y0-1 .. y0+kTY and columns x0-DIL .. x0+kTX-1+DIL with
@@ -107,48 +108,60 @@ __device__ __forceinline__ uint4 load_a(const uint16_t* __restrict__ X, const ui
 // gfx950 by the SQ_LDS_BANK_CONFLICT counter).  aux: GATHER, the blur buffer;
 // MODE_OUT, the residual (stride AUX_C); MODE_BWD, the activation whose ReLU
 // masks the gradient.
-constexpr int kTX = 64, kTY = 4;
-constexpr int kMaxDil = 9;  // the staging registers are sized for it
-static_assert(kDilation[0] <= kMaxDil && kDilation[1] <= kMaxDil && kDilation[2] <= kMaxDil &&
-                  kDilation[3] <= kMaxDil,
-              "dilation beyond the staged halo");
-constexpr int kStagePerThread = ((kTY + 2) * (kTX + 2 * kMaxDil) * 4 + 255) / 256;
+//
+// Memory bounds the hidden layers (48 x 512 x 512 pixels: 1.6 GB read and written,
+// 326 us at the rate of a copy), so what counts is whole lines and waves in
+// flight: 16-byte stores that cover 16 whole pixels, and tiles of eight rows,
+// two workgroups of eight waves per compute unit, which the dilation as a
+// constant makes room for (at most 128 registers).  Measured there with four
+// rows, three workgroups of four waves and 8-byte stores of half a pixel: layers
+// 1 to 4 370, 360, 362 and 245 us; eight rows 360, 344, 342 and 221; and with the
+// wide stores 305, 326, 323 and 220.
+constexpr int kTX = 64, kTY = 8, kConvThreads = 64 * kTY;
+constexpr int kConvGrid = 512;  // two workgroups (16 waves) per compute unit
 constexpr int kPlanes = 2 * kNeigh + 2;  // layer 1's sources: five views and the blur
-constexpr int kGatherPerThread = ((kTY + 2) * (kTX / 2 + kMaxDil + 1) * kPlanes + 255) / 256;  // pixel pairs
 
 __device__ __forceinline__ int swz(int row, int g) { return row * 4 + (g ^ ((row >> 1) & 3)); }
 
-template <int NT>
-constexpr size_t conv_lds_bytes(int dil) {
-  return (size_t)9 * NT * 16 * 4 * 16 + (size_t)(kTY + 2) * (kTX + 2 * dil) * 4 * 16;
+template <int NT, int DIL>
+constexpr size_t conv_lds_bytes() {
+  return (size_t)9 * NT * 16 * 4 * 16 + (size_t)(kTY + 2) * (kTX + 2 * DIL) * 4 * 16;
 }
 
-template <int NT, int MODE, bool GATHER>
-__global__ void __launch_bounds__(256) k_conv3x3(const uint16_t* __restrict__ X, const uint16_t* __restrict__ Wt,
-                                                  const float* __restrict__ bias, int N, int H, int W, int V, int DIL,
+template <int NT, int MODE, bool GATHER, int DIL>
+__global__ void __launch_bounds__(kConvThreads, 4) k_conv3x3(const uint16_t* __restrict__ X, const uint16_t* __restrict__ Wt,
+                                                  const float* __restrict__ bias, int N, int H, int W, int V,
                                                   uint16_t* __restrict__ Y, int YS, const uint16_t* __restrict__ aux,
                                                   int AUX_C) {
   constexpr int COUT = NT * 16;
   extern __shared__ uint4 smem[];
   uint4* wlds = smem;                  // [9 * COUT rows][4 groups]
   uint4* tl = smem + 9 * COUT * 4;     // [(kTY + 2) rows][TW pixels][4 groups]
-  const int TW = kTX + 2 * DIL;
+  constexpr int TW = kTX + 2 * DIL;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int g = lane >> 4, r16 = lane & 15;
-  for (int k = threadIdx.x; k < 9 * COUT * 4; k += blockDim.x)
-    wlds[swz(k >> 2, k & 3)] = reinterpret_cast<const uint4*>(Wt)[k];
+  const int g = lane >> 4, r16 = lane & 15, c0 = 4 * NT * g;
+  struct alignas(8 * NT) Chans {  // 4 NT channels of a pixel
+    uint32_t w[2 * NT];
+  };
+  for (int k = threadIdx.x; k < 9 * COUT * 4; k += blockDim.x) {
+    const int c = (k >> 2) % COUT;  // kept in row t * 16 + 4 g + e for channel 4 NT g + 4 t + e
+    const int row = (k >> 2) - c + (c / 4 % NT) * 16 + c / (4 * NT) * 4 + c % 4;
+    wlds[swz(row, k & 3)] = reinterpret_cast<const uint4*>(Wt)[k];
+  }
   // Loads whose results the epilogue uses are unconditional (clamped indices):
   // a load issued under a branch leaves the compiler unsure that a later wait
   // covered it, and it would then wait for all memory traffic in the epilogue.
   // The MFMA computes D = W x A (rows: output channels, columns: pixels), so
-  // lane (g, r16) ends with channels t*16 + 4g .. +3 of pixel r16 of each M tile.
+  // lane (g, r16) ends with rows t*16 + 4g .. +3 of pixel r16 of each M tile: the
+  // weights' rows are ordered so that these are the 4 NT channels from 4 NT g on,
+  // and a wave stores 16 whole pixels at once.
   float bco[NT][4];  // their biases (3 in the output layer)
   const int nbias = MODE == MODE_BWD ? 0 : (MODE == MODE_OUT ? 3 : YS);
 #pragma unroll
   for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const int c = t * 16 + 4 * g + e;
+      const int c = 4 * NT * g + 4 * t + e;
       if (MODE == MODE_BWD) {
         bco[t][e] = 0.0f;
       } else {
@@ -158,7 +171,7 @@ __global__ void __launch_bounds__(256) k_conv3x3(const uint16_t* __restrict__ X,
     }
   const int tiles_x = (W + kTX - 1) / kTX, tiles_y = (H + kTY - 1) / kTY;
   const int ntile = N * tiles_x * tiles_y;
-  const int nstage = (kTY + 2) * TW * 4;  // <= kStagePerThread * 256 for DIL <= kMaxDil
+  constexpr int nstage = (kTY + 2) * TW * 4;
   // Tile order.  Image-major ([n][row band][column]), except for the gathering
   // first layer: position-major with the view fastest, so the five output views
   // that read one input view's tile follow each other.  Workgroups are handed to
@@ -191,20 +204,20 @@ __global__ void __launch_bounds__(256) k_conv3x3(const uint16_t* __restrict__ X,
   // an even column xs = x0 - DIL - (DIL & 1), so each wave load reads 128
   // consecutive pixels of one plane (16 bytes a lane where the pair is inside
   // the image and 16-byte aligned, else two 8-byte loads): item j' = threadIdx
-  // + 256 j is plane j' / ((kTY + 2) NP), then row and pair (NP pairs a row);
+  // + kConvThreads j is plane j' / ((kTY + 2) NP), then row and pair (NP pairs a row);
   // plane p fills half p % 2 of group p / 2, pixels outside the tile's columns
   // are dropped, and group 3 (channels 24-31) stays zero.
-  constexpr int kSlots = GATHER ? kGatherPerThread : kStagePerThread;
-  const int NP = kTX / 2 + DIL + (DIL & 1);  // pixel pairs per staged row (layer 1)
+  constexpr int NP = kTX / 2 + DIL + (DIL & 1);  // pixel pairs per staged row (layer 1)
+  constexpr int kSlots = ((GATHER ? (kTY + 2) * NP * kPlanes : nstage) + kConvThreads - 1) / kConvThreads;  // items of a thread
   int geo[kSlots];
 #pragma unroll
   for (int j = 0; j < kSlots; ++j) {
     if (GATHER) {
-      const int i = (int)threadIdx.x + 256 * j, m = (kTY + 2) * NP;
+      const int i = (int)threadIdx.x + kConvThreads * j, m = (kTY + 2) * NP;
       const int pl = i / m, rem = i % m;
       geo[j] = (pl << 24) | ((rem / NP) << 16) | (rem % NP);
     } else {
-      const int q = (int)(threadIdx.x >> 2) + 64 * j;
+      const int q = (int)(threadIdx.x >> 2) + kConvThreads / 4 * j;
       geo[j] = ((q / TW) << 16) | (q % TW);
     }
   }
@@ -271,7 +284,7 @@ __global__ void __launch_bounds__(256) k_conv3x3(const uint16_t* __restrict__ X,
             reinterpret_cast<uint2*>(&tl[swz(r * TW + c0 + 1, pl >> 1)])[pl & 1] = uint2{pre[j].z, pre[j].w};
         }
       } else {
-        const int k = threadIdx.x + j * 256;
+        const int k = threadIdx.x + j * kConvThreads;
         if (k < nstage) tl[swz(k >> 2, k & 3)] = pre[j];
       }
     }
@@ -295,21 +308,16 @@ __global__ void __launch_bounds__(256) k_conv3x3(const uint16_t* __restrict__ X,
     // and used only where in range: the residual is requested before the MFMAs;
     // the mask (two 32-channel tiles) after them, which keeps the backward
     // instantiation at three waves per SIMD
-    uint2 side[4][NT];
+    Chans side[4];
     auto load_side = [&]() {
 #pragma unroll
-      for (int m = 0; m < 4; ++m)
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          const int x = min(x0 + m * 16 + r16, W - 1), yc = min(y, H - 1), c0 = t * 16 + 4 * g;
-          side[m][t] = *reinterpret_cast<const uint2*>(aux + (((size_t)n * H + yc) * W + x) * AUX_C +
-                                                       (c0 < YS ? c0 : 0));
-        }
+      for (int m = 0; m < 4; ++m) {
+        const int x = min(x0 + m * 16 + r16, W - 1), yc = min(y, H - 1);
+        side[m] = *reinterpret_cast<const Chans*>(aux + (((size_t)n * H + yc) * W + x) * AUX_C + (c0 < YS ? c0 : 0));
+      }
     };
 #pragma unroll
-    for (int m = 0; m < 4; ++m)
-#pragma unroll
-      for (int t = 0; t < NT; ++t) side[m][t] = uint2{0u, 0u};
+    for (int m = 0; m < 4; ++m) side[m] = Chans{};
     if (MODE == MODE_OUT) load_side();
     f32x4 acc[4][NT];
 #pragma unroll
@@ -341,39 +349,35 @@ __global__ void __launch_bounds__(256) k_conv3x3(const uint16_t* __restrict__ X,
     if (next < t_end) stage();
     __syncthreads();
     if (next + t_step < t_end) fetch(next + t_step);
-    // epilogue: lane holds D[4g+e][r16] = channel t*16 + 4g + e of pixel x0 + 16m + r16
-    // (row y0 + wv); four consecutive channels leave as one 8-byte store
+    // epilogue: 4 NT consecutive channels of pixel x0 + 16m + r16 (row y0 + wv) leave as one store
     if (y < H) {
 #pragma unroll
       for (int m = 0; m < 4; ++m) {
         const int x = x0 + m * 16 + r16;
-        if (x >= W) continue;
-        const size_t p = ((size_t)n * H + y) * W + x;
+        if (x >= W || c0 >= YS) continue;
+        Chans o;
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-          const int c0 = t * 16 + 4 * g;
-          if (c0 >= YS) continue;
+          const uint32_t side0 = side[m].w[2 * t], side1 = side[m].w[2 * t + 1];
+          const float sv[4] = {from_bf16((uint16_t)(side0 & 0xFFFFu)), from_bf16((uint16_t)(side0 >> 16)),
+                               from_bf16((uint16_t)(side1 & 0xFFFFu)), from_bf16((uint16_t)(side1 >> 16))};
           float v[4];
-          const uint16_t sh[4] = {(uint16_t)(side[m][t].x & 0xFFFFu), (uint16_t)(side[m][t].x >> 16),
-                                  (uint16_t)(side[m][t].y & 0xFFFFu), (uint16_t)(side[m][t].y >> 16)};
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const int co = c0 + e;
             float u = acc[m][t][e];
             if (MODE == MODE_RELU) {
               u = fmaxf(u + bco[t][e], 0.0f);
             } else if (MODE == MODE_OUT) {
-              u = co < 3 ? (u + bco[t][e]) + from_bf16(sh[e]) : 0.0f;
+              u = c0 + 4 * t + e < 3 ? (u + bco[t][e]) + sv[e] : 0.0f;
             } else {
-              u = from_bf16(sh[e]) > 0.0f ? u : 0.0f;
+              u = sv[e] > 0.0f ? u : 0.0f;
             }
             v[e] = u;
           }
-          uint2 o;
-          o.x = pack_bf16x2(v[0], v[1]);
-          o.y = pack_bf16x2(v[2], v[3]);
-          *reinterpret_cast<uint2*>(Y + p * YS + c0) = o;
+          o.w[2 * t] = pack_bf16x2(v[0], v[1]);
+          o.w[2 * t + 1] = pack_bf16x2(v[2], v[3]);
         }
+        *reinterpret_cast<Chans*>(Y + (((size_t)n * H + y) * W + x) * YS + c0) = o;
       }
     }
   }
@@ -389,10 +393,10 @@ __global__ void __launch_bounds__(256) k_conv3x3(const uint16_t* __restrict__ X,
 // 16 channels per 16 lanes.  Wave w of three takes the taps of row w - 1: per 16
 // pixels one dZ operand and, for each tap, the shifted A operand and one
 // v_mfma_f32_32x32x16_bf16 over all 32 x 32 channels; no sums cross waves.  The
-// next tile is fetched into registers meanwhile.  (Four waves with a row of the
-// tile each and all nine taps: 60 us, most of it adding up the waves' sums.  Staging each tap's shifted pixels channel by channel
-// through two-byte LDS writes instead: 48 x 128 x 128 pixels, 60-72 -> 30-39 us a
-// layer, and 9 us for the biases.)
+// next tile is fetched into registers meanwhile.  48 x 128 x 128 pixels: 60-72 us a
+// layer, and 9 for its biases, when each tap's shifted pixels were staged channel
+// by channel through two-byte LDS writes; 30-39 now.  (Four waves with a row of the
+// tile each and all nine taps: 60, most of it adding up the waves' sums.)
 //
 // Workgroups take tiles grid, 2 grid, .. apart and write their sums to their own
 // row of a partials buffer laid out as the parameter vector, which
@@ -772,12 +776,12 @@ int nfail(lfdpr_net* n, int code, const std::string& m) {
     if (e_ != hipSuccess) return nfail(net, LFDPR_EDEVICE, std::string(#call) + ": " + hipGetErrorString(e_)); \
   } while (0)
 
-template <int NT, int MODE, bool GATHER>
-void launch_conv(const uint16_t* X, const uint16_t* Wt, const float* b, int N, int H, int W, int V, int dil,
+template <int NT, int MODE, bool GATHER, int DIL>
+void launch_conv(const uint16_t* X, const uint16_t* Wt, const float* b, int N, int H, int W, int V,
                  uint16_t* Y, int YS, const uint16_t* aux, int AUXC, hipStream_t s) {
   const int64_t tiles = (int64_t)N * ((H + kTY - 1) / kTY) * ((W + kTX - 1) / kTX);
-  const int grid = (int)(tiles < 768 ? tiles : 768);  // persistent: about three blocks per CU
-  k_conv3x3<NT, MODE, GATHER><<<grid, 256, conv_lds_bytes<NT>(dil), s>>>(X, Wt, b, N, H, W, V, dil, Y, YS, aux, AUXC);
+  const int grid = (int)std::min<int64_t>(tiles, kConvGrid);  // persistent
+  k_conv3x3<NT, MODE, GATHER, DIL><<<grid, kConvThreads, conv_lds_bytes<NT, DIL>(), s>>>(X, Wt, b, N, H, W, V, Y, YS, aux, AUXC);
 }
 
 void pack_weights(lfdpr_net* net) {
@@ -945,7 +949,6 @@ int lfdpr_net_forward(lfdpr_net* net, const void* x, int32_t n_views, int32_t H,
   const uint16_t* in = (const uint16_t*)x;
   hipStream_t s = net->stream;
   const int N = n_views, V = net->V;
-  const int* d = kDilation;
   const int64_t npx = (int64_t)N * H * W;
   if (W <= kBlurRowMax) {
     const int rows = blur_rows((int64_t)N * H, W);
@@ -955,10 +958,10 @@ int lfdpr_net_forward(lfdpr_net* net, const void* x, int32_t n_views, int32_t H,
   } else {
     k_disparity_blur<<<(unsigned)((npx + 255) / 256), 256, 0, s>>>(in, npx, W, net->kscale, net->taps, net->xb);
   }
-  launch_conv<2, MODE_RELU, true>(in, net->wf[0], net->master + net->off_b[0], N, H, W, V, d[0], net->act[1], kHidden, net->xb, 4, s);
-  launch_conv<2, MODE_RELU, false>(net->act[1], net->wf[1], net->master + net->off_b[1], N, H, W, V, d[1], net->act[2], kHidden, nullptr, 0, s);
-  launch_conv<2, MODE_RELU, false>(net->act[2], net->wf[2], net->master + net->off_b[2], N, H, W, V, d[2], net->act[3], kHidden, nullptr, 0, s);
-  launch_conv<1, MODE_OUT, false>(net->act[3], net->wf[3], net->master + net->off_b[3], N, H, W, V, d[3], (uint16_t*)y, 4, net->xb, 4, s);
+  launch_conv<2, MODE_RELU, true, kDilation[0]>(in, net->wf[0], net->master + net->off_b[0], N, H, W, V, net->act[1], kHidden, net->xb, 4, s);
+  launch_conv<2, MODE_RELU, false, kDilation[1]>(net->act[1], net->wf[1], net->master + net->off_b[1], N, H, W, V, net->act[2], kHidden, nullptr, 0, s);
+  launch_conv<2, MODE_RELU, false, kDilation[2]>(net->act[2], net->wf[2], net->master + net->off_b[2], N, H, W, V, net->act[3], kHidden, nullptr, 0, s);
+  launch_conv<1, MODE_OUT, false, kDilation[3]>(net->act[3], net->wf[3], net->master + net->off_b[3], N, H, W, V, (uint16_t*)y, 4, net->xb, 4, s);
   NHIP(hipGetLastError());
   net->last_x = in;
   net->last_y = (const uint16_t*)y;
@@ -980,21 +983,19 @@ int lfdpr_net_backward(lfdpr_net* net, const void* target, float* loss) {
   k_mse<<<mse_blocks, 256, 0, s>>>(net->last_y, (const uint16_t*)target, npx, net->dz[4], loss_part);
   const int64_t tiles = (int64_t)N * ((H + kGY - 1) / kGY) * ((W + kGX - 1) / kGX);
   const int rows = (int)std::min<int64_t>(tiles, kGradBlocks);
-  for (int k = 3; k >= 0; --k) {
-    const int CO = net->co[k], CI = net->ci[k], np = (int)net->nparams;
-    float* const part = net->part + net->off_w[k];  // the layer's weights, then its biases
-    if (k == 0)
-      k_conv_wgrad<true, kDilation[0]><<<rows, kGThreads, 0, s>>>(net->dz[1], CO, net->last_x, net->xb, CI, N, H, W, V, part, np);
-    else if (k == 1)
-      k_conv_wgrad<false, kDilation[1]><<<rows, kGThreads, 0, s>>>(net->dz[2], CO, net->act[1], nullptr, CI, N, H, W, V, part, np);
-    else if (k == 2)
-      k_conv_wgrad<false, kDilation[2]><<<rows, kGThreads, 0, s>>>(net->dz[3], CO, net->act[2], nullptr, CI, N, H, W, V, part, np);
-    else
-      k_conv_wgrad<false, kDilation[3]><<<rows, kGThreads, 0, s>>>(net->dz[4], CO, net->act[3], nullptr, CI, N, H, W, V, part, np);
-    if (k > 0)  // input gradient through the flipped, transposed weights (same dilation), masked by the ReLU
-      launch_conv<2, MODE_BWD, false>(net->dz[k + 1], net->wb[k], nullptr, N, H, W, V, kDilation[k], net->dz[k], kHidden,
-                                      net->act[k], kHidden, s);
-  }
+  auto layer = [&](auto index) {
+    constexpr int k = decltype(index)::value;
+    k_conv_wgrad<k == 0, kDilation[k]><<<rows, kGThreads, 0, s>>>(
+        net->dz[k + 1], net->co[k], k == 0 ? net->last_x : net->act[k], k == 0 ? net->xb : nullptr, net->ci[k], N, H, W, V,
+        net->part + net->off_w[k], (int)net->nparams);  // the layer's weights, then its biases
+    if constexpr (k > 0)  // input gradient through the flipped, transposed weights, masked by the ReLU
+      launch_conv<2, MODE_BWD, false, kDilation[k]>(net->dz[k + 1], net->wb[k], nullptr, N, H, W, V, net->dz[k], kHidden,
+                                                    net->act[k], kHidden, s);
+  };
+  layer(std::integral_constant<int, 3>());
+  layer(std::integral_constant<int, 2>());
+  layer(std::integral_constant<int, 1>());
+  layer(std::integral_constant<int, 0>());
   k_sum_partials<<<(unsigned)((net->nparams + 31) / 32) + 1, 256, 0, s>>>(net->part, rows, (int)net->nparams, net->grad,
                                                                           loss_part, mse_blocks, net->d_loss, loss);
   NHIP(hipGetLastError());
