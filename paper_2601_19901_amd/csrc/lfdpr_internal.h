@@ -8,7 +8,7 @@
 namespace lfdpr {
 
 enum StatSlot { STAT_ACTIVE = 0, STAT_OVERFLOW = 1, STAT_POINT_VIEWS = 2, STAT_TOTAL = 3, STAT_BIG = 4,
-                STAT_WRITTEN = 5, STAT_EMITTING = 6, STAT_COVERED = 7, STAT_SLOTS = 8 };
+                STAT_WRITTEN = 5, STAT_EMITTING = 6, STAT_COVERED = 7, STAT_TICKET = 8, STAT_SLOTS = 9 };
 
 // The statistics buffer continues with 64 lines of 128 bytes, cleared with it at
 // the start of a frame: the counter of a work queue of the point splat, and
@@ -64,6 +64,7 @@ struct SetupArgs {
   uint64_t* tile_stat; // and their statistics: point-views | active << 36 | overflowed << 50
   uint32_t* big;       // triangles with more than kBigCells cells (capacity nt)
   uint64_t* n_big;     // and their number
+  uint32_t* ticket;    // set by launch_tri_setup: workgroups that have stored their sums, or null
 };
 
 struct EmitArgs {

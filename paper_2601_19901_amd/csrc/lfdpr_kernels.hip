@@ -464,6 +464,28 @@ __global__ void __launch_bounds__(256) k_tri_setup(SetupArgs a) {
     a.tile_sum[blockIdx.x] = points;
     a.tile_stat[blockIdx.x] = stat;
   }
+  if (kVL == 8 && a.ticket) {  // the last workgroup to get here does the work of k_scan_top
+    __shared__ bool last;
+    if (threadIdx.x == 0)
+      last = __hip_atomic_fetch_add(a.ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+    __syncthreads();
+    if (!last) return;
+    uint64_t sum = 0, q = 0;
+    if (threadIdx.x < gridDim.x) {
+      sum = __hip_atomic_load(a.tile_sum + threadIdx.x, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
+      q = __hip_atomic_load(a.tile_stat + threadIdx.x, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    const uint64_t base = block_excl_scan(sum, ws4);
+    if (threadIdx.x < gridDim.x) a.tile_sum[threadIdx.x] = base;
+    const uint64_t all = block_sum(sum, ws4), pv = block_sum(q & ((1ull << 36) - 1), ws4);
+    const uint64_t act = block_sum((q >> 36) & 0x3FFFu, ws4), over = block_sum(q >> 50, ws4);
+    if (threadIdx.x == 0) {
+      a.stats[STAT_TOTAL] = all;
+      a.stats[STAT_POINT_VIEWS] = pv;
+      a.stats[STAT_ACTIVE] = act;
+      a.stats[STAT_OVERFLOW] = over;
+    }
+  }
 }
 
 // ------------------------------------------------------------------ scan (counts -> offsets)
@@ -471,9 +493,9 @@ __global__ void __launch_bounds__(256) k_tri_setup(SetupArgs a) {
 // set-up workgroup writes the sum of its triangles, k_scan_top turns the sums
 // into bases (one workgroup; also the grand total), and the emission kernel
 // adds the prefix within its tile of 256 triangles (one or eight workgroups of
-// the set-up).
-
-
+// the set-up).  Up to kScanTiles set-up workgroups, one sum per thread, the last
+// of them to finish does it instead of a launch (a frame of 1,280 triangles 53.1
+// -> 51.4 us).
 __global__ void __launch_bounds__(1024) k_scan_top(uint64_t* __restrict__ tile_sum,
                                                     const uint64_t* __restrict__ tile_stat, int64_t ntiles,
                                                     uint64_t* __restrict__ stats) {
@@ -2140,8 +2162,14 @@ constexpr int64_t kSplitTris = 131072;
 
 int setup_lanes(int64_t nt) { return nt < kSplitTris ? 8 : 1; }
 
-void launch_tri_setup(const SetupArgs& a, hipStream_t s) {
-  if (a.nt <= 0) return;
+// Set-up workgroups whose sums the last of them scans.
+constexpr unsigned kScanTiles = 256;
+static bool setup_scans(int64_t nt) { return nt > 0 && setup_lanes(nt) == 8 && nblk(nt, 256 / 8) <= kScanTiles; }
+
+void launch_tri_setup(const SetupArgs& args, hipStream_t s) {
+  if (args.nt <= 0) return;
+  SetupArgs a = args;
+  a.ticket = setup_scans(a.nt) ? reinterpret_cast<uint32_t*>(a.stats + STAT_TICKET) : nullptr;
   const int vl = setup_lanes(a.nt);
   const unsigned g = nblk(a.nt, 256 / vl);
   if (a.n_items > 1 && vl == 8)
@@ -2166,6 +2194,7 @@ void launch_interleave_batch(const InterleaveArgs& a, int n_items, int64_t view_
 
 void launch_scan(uint64_t* tile_sum, const uint64_t* tile_stat, int64_t nt, uint64_t* stats, hipStream_t s) {
   const int64_t per = 256 / setup_lanes(nt);
+  if (setup_scans(nt)) return;
   k_scan_top<<<1, 1024, 0, s>>>(tile_sum, tile_stat, (nt + per - 1) / per, stats);
 }
 

@@ -56,3 +56,26 @@ def test_setup_and_emission_match_the_oracle(torch_cuda, n, W, H, V, fovy, znear
     assert g["stats"]["overflow_tris"] == o["stats"]["overflow_tris"]
     # covered pixels but those of triangles without points (overflowed lattices) and those outside their splat
     assert g["stats"]["written_px"] == o["stats"]["fragments"] - o["stats"]["misses"] - o["stats"]["orphans"]
+
+
+@pytest.mark.parametrize("n", [8160, 8192, 8193, 8225])
+def test_totals_around_the_scan_in_the_set_up(torch_cuda, n):
+    """Up to 256 set-up workgroups (8,192 triangles) the last one scans the
+    point counts; from there on a launch of its own does.  Frames one after the
+    other on one context give the oracle's points and statistics each time."""
+    from paper_2601_19901_amd import lfdpr
+    scene = _first(scenes.display_scene(5, hf_quads=70, levels=(2, 1), counts=(57, 143), tex_size=8, n_tex=2), n)
+    assert scene.n_tris == n
+    vp = scenes.ViewParams(V=5, W=96, H=80, fovy_deg=30.0, aspect=1.6, D=10.0, cone_deg=40.0, znear=0.5)
+    w = scenes.Workload("scan", scene, vp, None)
+    R = lfdpr.Renderer(0)
+    sid = R.upload_scene(scene)
+    R.set_views(vp)
+    for angle in (-55.0, 20.0, -55.0):
+        model = scenes.model_matrix(3, 10.0, angle)
+        o = O.render(scene, vp, model)
+        g = run_gpu(R, sid, w, model, n)
+        print(f"[n {n} angle {angle}] {g['stats']}", flush=True)
+        assert_parity(g, o, n, f"scan n {n}")
+        for key in ("active_tris", "point_views", "overflow_tris"):
+            assert g["stats"][key] == o["stats"][key]
