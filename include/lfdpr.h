@@ -358,7 +358,7 @@ int lfdpr_get_timings(lfdpr_ctx* ctx, double* ms_sum, int64_t* n_launches);
  * Launch shape, autotuning and batches (not part of the paper).
  * ------------------------------------------------------------------------ */
 typedef struct {
-  int32_t splat_blocks;  /* workgroups of the splat and fetch launches */
+  int32_t splat_blocks;  /* workgroups of the splat (at most 1024 under the point order) and fetch launches */
   int32_t key_layout;    /* 0: 64-bit keys [view][y][x]; 1: [y][view][x] (a row of every view adjacent) */
   float ms;              /* measured time of one frame (or one batch) */
   int32_t splat_order;   /* LFDPR_SPLAT_POINT or LFDPR_SPLAT_QUILT (single frames) */
