@@ -846,6 +846,15 @@ int lfdpr_net_create(lfdpr_ctx* ctx, int32_t V, int32_t max_h, int32_t max_w, lf
     lfdpr_net_destroy(net);
     return LFDPR_ENOMEM;
   }
+  // the widest dilation's staged tile takes 71 KB, above the 64 KB a launch has by default
+  constexpr int wide = (int)conv_lds_bytes<2, kDilation[2]>();
+  if (hipFuncSetAttribute((const void*)k_conv3x3<2, MODE_RELU, false, kDilation[2]>,
+                          hipFuncAttributeMaxDynamicSharedMemorySize, wide) != hipSuccess ||
+      hipFuncSetAttribute((const void*)k_conv3x3<2, MODE_BWD, false, kDilation[2]>,
+                          hipFuncAttributeMaxDynamicSharedMemorySize, wide) != hipSuccess) {
+    lfdpr_net_destroy(net);
+    return LFDPR_EDEVICE;
+  }
   if (hipMemset(net->master, 0, off * 4) != hipSuccess) {
     lfdpr_net_destroy(net);
     return LFDPR_EDEVICE;
