@@ -371,12 +371,12 @@ SplatArgs quilt_tile_args(const SplatArgs& pa, const QuiltBinArgs& qa, PointBox*
   qp.q_bands_item = qa.bands_item;
   qp.q_subsets = (pa.table_rig.n_views + views - 1) / views;
   // two tiles per CU when their LDS allows (the device's per-workgroup
-  // figure is the CU's LDS on this architecture); the waves' queues of
-  // covered pixels wherever they fit beside the tile
+  // figure is the CU's LDS on this architecture) with the waves' queues of
+  // covered pixels beside them; one tile keeps its queues in LDS where they
+  // fit, else in registers
   const size_t tile = quilt_lds_bytes(qa.rows, views, pa.table_rig.W, pa.table_rig.H), lds = (size_t)max_lds;
   qp.q_block = 2 * (tile + quilt_queue_bytes(512)) <= lds ? 512 : 1024;
   qp.q_queue = tile + quilt_queue_bytes(qp.q_block) <= lds;
-  if (!qp.q_queue && 2 * tile <= lds) qp.q_block = 512;
   qp.out_rgba = out_rgba;
   qp.out_depth = out_depth;
   return qp;

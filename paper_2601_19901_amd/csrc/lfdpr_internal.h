@@ -128,7 +128,7 @@ struct SplatArgs {
   int32_t q_rows, q_views, q_bands, q_subsets;  // tile: q_rows rows x q_views views x W
   int32_t q_bands_item;        // bands per item (q_bands over all items)
   int32_t q_block;             // threads per quilt workgroup: 1024, or 512 (two tiles per CU)
-  int32_t q_queue;             // 1: the tile's LDS also holds its waves' covered-pixel queues
+  int32_t q_queue;             // 1: the tile's LDS also holds its waves' covered-pixel queues (else registers do)
   uint32_t* out_rgba;          // the views, [view][y][x]
   float* out_depth;            // optional, [view][y][x]
 };
