@@ -467,6 +467,7 @@ __global__ void __launch_bounds__(kGThreads) k_conv_wgrad(const uint16_t* __rest
       if ((int)threadIdx.x + kGThreads * j < kAPix * 4) reinterpret_cast<uint4*>(at)[threadIdx.x + kGThreads * j] = pa[j];
     __syncthreads();
     if (tile + (int)gridDim.x < ntile) fetch(tile + gridDim.x);
+    float btile = 0.f;  // the tile's terms first: a workgroup may take hundreds of tiles
 #pragma unroll
     for (int row = 0; row < kGY; ++row)
 #pragma unroll
@@ -474,13 +475,14 @@ __global__ void __launch_bounds__(kGThreads) k_conv_wgrad(const uint16_t* __rest
         const bf16x8 fz = read_pixels(zt + (row * kGX + 16 * k + px) * kK + ch);
         if (wv == 0)
 #pragma unroll
-          for (int e = 0; e < 8; ++e) bsum += (float)fz[e];
+          for (int e = 0; e < 8; ++e) btile += (float)fz[e];
 #pragma unroll
         for (int t = 0; t < 3; ++t) {
           const bf16x8 fa = read_pixels(at + ((row + wv) * TW + 16 * k + t * DIL + px) * kK + ch);
           acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fz, fa, acc[t], 0, 0, 0);
         }
       }
+    bsum += btile;
   }
   // lane holds D[8 (e / 4) + 4 (lane / 32) + e % 4][lane % 32]
   float* const out = part + (size_t)blockIdx.x * part_row;
