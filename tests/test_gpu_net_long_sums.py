@@ -56,3 +56,19 @@ def test_bias_gradient_keeps_small_terms(net):
     err = np.abs(G[3][1] - want) / want
     print("bias gradient, relative errors", err)
     assert (err < 714 * 2.0 ** -24).all()
+
+
+def test_weight_gradient_keeps_small_terms(net):
+    """128 products of eight tiles (two roundings each), 64 such sums, 64 rows and 8 phases of partial sums: at most 392
+    roundings, which a matrix accumulator may do towards zero."""
+    _, G = backward(net[0], DZ_HEAD, DZ_TAIL)
+    dz = np.zeros((2, 3, 3))  # pixels that tap (r, c) sees inside the view: in the head, after it
+    for r in range(3):
+        for c in range(3):
+            w = W - abs(c - 1)
+            head = (HEAD - 1 if r == 0 else HEAD) * w
+            dz[:, r, c] = head, V * (H - abs(r - 1)) * w - head
+    want = ((dz[0] + dz[1] * 1.25 * 2.0 ** -18) * 2.0 / PX).reshape(9, 1, 1)
+    err = np.abs(G[3][0] - want) / want
+    print("weight gradient, largest relative error", err.max())
+    assert err.max() < 392 * 2.0 ** -23
