@@ -517,8 +517,9 @@ __global__ void __launch_bounds__(kGThreads, 2) k_conv_wgrad(const uint16_t* __r
 // out[i] = sum over the nblk rows of part[b][i] in a fixed order: in a block of
 // 256, lane (phase f = t / 32, column j = t % 32) adds rows f, f + 8, .. in
 // ascending order, then the 8 phase sums of each column are added in phase
-// order.  The last workgroup adds the loss's nloss partial sums the same way and
-// writes it to *loss0 and, if given, *loss1.  Grid: ceil(n / 32) + 1 blocks.
+// order.  The last workgroup adds the loss's nloss partial sums (lane t those of
+// t, t + 256, .., then the lanes' by halves) and writes it to *loss0 and, if
+// given, *loss1.  Grid: ceil(n / 32) + 1 blocks.
 __global__ void __launch_bounds__(256) k_sum_partials(const float* __restrict__ part, int nblk, int n,
                                                        float* __restrict__ out, const float* __restrict__ loss_part,
                                                        int nloss, float* __restrict__ loss0, float* __restrict__ loss1) {
@@ -536,11 +537,14 @@ __global__ void __launch_bounds__(256) k_sum_partials(const float* __restrict__ 
   red[f][j] = sum;
   __syncthreads();
   if (last) {
+    float* const r = red[0];
+    for (int k = 128; k > 0; k >>= 1) {
+      if ((int)threadIdx.x < k) r[threadIdx.x] += r[threadIdx.x + k];
+      __syncthreads();
+    }
     if (threadIdx.x == 0) {
-      float total = 0.0f;
-      for (int k = 0; k < 256; ++k) total += red[k >> 5][k & 31];
-      *loss0 = total;
-      if (loss1) *loss1 = total;
+      *loss0 = r[0];
+      if (loss1) *loss1 = r[0];
     }
   } else if (f == 0 && i < n) {
     float total = 0.0f;
@@ -552,12 +556,15 @@ __global__ void __launch_bounds__(256) k_sum_partials(const float* __restrict__ 
 // loss = mean((y - t)^2) over the 3 colour channels of npx pixels (inputs
 // [p][4]), as one partial sum per workgroup; dZ = bf16(2 (y - t) / n) into a
 // [p][32] buffer (other channels 0).  Four lanes per pixel, one 16-byte store
-// each, so that a wave writes 1 KiB in a row.
+// each, so that a wave writes 1 KiB in a row.  16 pixels' squares are summed
+// before they join a lane's sum (up to 512 pixels a lane: 64 views of
+// 1024 x 1024 -5.4e-6 of the loss in one chain).
 constexpr int kMseBlocks = 2048;
 __global__ void __launch_bounds__(256) k_mse(const uint16_t* __restrict__ Yb, const uint16_t* __restrict__ T, int npx,
                                               uint16_t* __restrict__ dZ, float* __restrict__ loss_part) {
   const int64_t n = (int64_t)npx * 3;
-  float sq = 0.0f;
+  float sq = 0.0f, run = 0.0f;
+  int k = 0;
   const int g = threadIdx.x & 3;
   for (int64_t p = (int64_t)blockIdx.x * 64 + (threadIdx.x >> 2); p < npx; p += (int64_t)gridDim.x * 64) {
     uint4 o{0u, 0u, 0u, 0u};
@@ -567,16 +574,18 @@ __global__ void __launch_bounds__(256) k_mse(const uint16_t* __restrict__ Yb, co
       const float d0 = from_bf16((uint16_t)(yv.x & 0xFFFFu)) - from_bf16((uint16_t)(tv.x & 0xFFFFu));
       const float d1 = from_bf16((uint16_t)(yv.x >> 16)) - from_bf16((uint16_t)(tv.x >> 16));
       const float d2 = from_bf16((uint16_t)(yv.y & 0xFFFFu)) - from_bf16((uint16_t)(tv.y & 0xFFFFu));
-      sq += d0 * d0;
-      sq += d1 * d1;
-      sq += d2 * d2;
+      run += (d0 * d0 + d1 * d1) + d2 * d2;
+      if ((++k & 15) == 0) {
+        sq += run;
+        run = 0.0f;
+      }
       o.x = (uint32_t)to_bf16((2.0f * d0) / (float)n) | ((uint32_t)to_bf16((2.0f * d1) / (float)n) << 16);
       o.y = (uint32_t)to_bf16((2.0f * d2) / (float)n);
     }
     reinterpret_cast<uint4*>(dZ + p * kK)[g] = o;
   }
   __shared__ float red[256];
-  red[threadIdx.x] = sq;
+  red[threadIdx.x] = sq + run;
   __syncthreads();
   for (int k = 128; k > 0; k >>= 1) {
     if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];

@@ -72,3 +72,15 @@ def test_weight_gradient_keeps_small_terms(net):
     err = np.abs(G[3][0] - want) / want
     print("weight gradient, largest relative error", err.max())
     assert err.max() < 392 * 2.0 ** -23
+
+
+def test_loss_keeps_small_terms(net):
+    """2,048 workgroups, a lane per pixel: its first is in the head, with squares 2^24 times those of the 511 after it.
+    Three squares of a pixel, 16 pixels, 32 such sums, then halves of 64 lanes, 8 workgroups and halves of 256: at most
+    72 roundings, and those of the division by the number of terms."""
+    head = 4096.0
+    loss, _ = backward(net[0], head, 1.0)
+    n_head = HEAD * W
+    want = (n_head * head ** 2 + (PX - n_head)) / PX
+    print("loss, relative error", loss / want - 1.0)
+    assert abs(loss / want - 1.0) < 74 * 2.0 ** -24
