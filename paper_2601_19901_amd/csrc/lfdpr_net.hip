@@ -698,9 +698,9 @@ inline int blur_rows(int64_t nrows, int W) {
 }
 
 __global__ void __launch_bounds__(256) k_disparity_blur_rows(const uint16_t* __restrict__ X, int64_t nrows, int W, int R,
-                                                              float k, BlurTaps bw, uint16_t* __restrict__ XB) {
+                                                              int4 st, float k, BlurTaps bw, uint16_t* __restrict__ XB) {
   extern __shared__ Colour lrow[];  // R rows of W + 3 pixels: pixel i at i + 1
-  const int P = W + 3;
+  const int P = W + 3;  // st: 256 pixels are st.x rows and st.y pixels of W, st.z rows and st.w of P
   const int64_t ngroups = (nrows + R - 1) / R;
   for (int64_t gr = blockIdx.x; gr < ngroups; gr += gridDim.x) {
     const int64_t r0 = gr * R;
@@ -710,7 +710,9 @@ __global__ void __launch_bounds__(256) k_disparity_blur_rows(const uint16_t* __r
     __syncthreads();  // the previous group's gathers are finished
     for (int i = threadIdx.x, r = i / P, c = i % P; r < nr; i += blockDim.x) {
       lrow[i] = unpack_colour(src[r * W + min(max(c - 1, 0), W - 1)]);
-      for (c += blockDim.x; c >= P; c -= P) ++r;
+      r += st.z;
+      c += st.w;
+      if (c >= P) { c -= P; ++r; }
     }
     __syncthreads();
     for (int i = threadIdx.x, r = i / W, x = i % W; r < nr; i += blockDim.x) {
@@ -721,7 +723,9 @@ __global__ void __launch_bounds__(256) k_disparity_blur_rows(const uint16_t* __r
             cb = row[a + 1];
           },
           src[i].y, x, W, k, bw);
-      for (x += blockDim.x; x >= W; x -= W) ++r;
+      r += st.x;
+      x += st.y;
+      if (x >= W) { x -= W; ++r; }
     }
   }
 }
@@ -990,7 +994,7 @@ int lfdpr_net_forward(lfdpr_net* net, const void* x, int32_t n_views, int32_t H,
     const int rows = blur_rows((int64_t)N * H, W);
     const int64_t groups = ((int64_t)N * H + rows - 1) / rows;
     k_disparity_blur_rows<<<(unsigned)(groups < 4096 ? groups : 4096), 256, (size_t)rows * (W + 3) * sizeof(Colour), s>>>(
-        in, (int64_t)N * H, W, rows, net->kscale, net->taps, net->xb);
+        in, (int64_t)N * H, W, rows, int4{256 / W, 256 % W, 256 / (W + 3), 256 % (W + 3)}, net->kscale, net->taps, net->xb);
   } else {
     k_disparity_blur<<<(unsigned)((npx + 255) / 256), 256, 0, s>>>(in, npx, W, net->kscale, net->taps, net->xb);
   }
