@@ -1383,9 +1383,12 @@ __device__ __forceinline__ void splat_wave(const Item& item, bool valid, uint64_
 // 3.0M points, 48 views of 512 x 512): all views 440 and 1505 us, this rule 420
 // and 1455, twice as many items 438 and 1455.
 // The parts follow each other, all chunks in one part of the views before the
-// next, and a part's keys are at most kReachKeys (192 MiB, within the 256 MiB
-// last-level cache, where the updates are resolved): 48 views of 1024 x 1024 in
-// one part 3.43 ms, in three 3.37.
+// next (in a batch, one item's after the other's), and there are as many as the
+// keys of all views take kReachKeys (192 MiB, so that a part's updates are
+// resolved in the 256 MiB last-level cache), a part's views rounded up: 48 views
+// of 1024 x 1024 in one part 4.15 ms, in two 3.39.  Large views: 5 of 4096 x 4096
+// in parts of two views (256 MiB of keys) 5.51 ms, of one 6.02, since each part
+// repeats the points' set-up.
 constexpr uint64_t kReachKeys = 24ull << 20;
 constexpr uint32_t kFillItems = 32768;
 
