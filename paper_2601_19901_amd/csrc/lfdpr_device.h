@@ -212,11 +212,13 @@ LF_HD bool may_be_seen(const Rig& rg, const TriRec& R) {
 
 // Correctly rounded binary32 quotients and roots for operands in the middle of
 // the range (|a| zero or in 2^-100 .. 2^100, |b| in 2^-100 .. 2^100, their
-// quotient in 2^-100 .. 2^100, x zero or in 2^-90 .. 2^90):
-// the reciprocal, two residual corrections and, for the root, the choice among
-// three neighbours by their residuals, which is what `/` and sqrtf come to there
-// without their scaling and special cases.  A divisor's reciprocal is shared
-// by all of its quotients.  Host: the plain operators.
+// quotient in 2^-100 .. 2^100, x zero or in 2^-90 .. 2^90): the reciprocal and
+// two corrections by the fused residual (Markstein, IBM J. Res. Dev. 34, 1990)
+// and, for the root, the choice among three neighbours by the sign of their
+// products' residuals (Tuckerman's rounding test, in the same paper), which is
+// what `/` and sqrtf come to there without their scaling and special cases.  A
+// divisor's reciprocal is shared by all of its quotients.  Host: the plain
+// operators.
 struct Divisor {
   float b, y;
 };
@@ -253,9 +255,11 @@ LF_HD float root(float x) {
 // edges and face (Ericson, Real-Time Collision Detection, Sec. 5.1.5): the
 // region gives the numerator and denominator of one quotient (1 / the sum of
 // areas on the face), so that lanes in different regions divide together.
-// kPlain: by quotient() where its operands are in the middle of the range.
+// kPlain: by quotient() where its operands and result are in the middle of the
+// range.  Sets *odd if the quotient is not finite (the areas of a microscopic
+// triangle underflow): the point then is not on the triangle.
 template <bool kPlain>
-LF_HD F3 nearest_on_triangle(F3 p, F3 a, F3 b, F3 c) {
+LF_HD F3 nearest_on_triangle(F3 p, F3 a, F3 b, F3 c, uint32_t* odd) {
   const F3 ab = sub3(b, a), ac = sub3(c, a);
   const F3 ap = sub3(p, a), bp = sub3(p, b), cp = sub3(p, c);
   const float d1 = dot3(ab, ap), d2 = dot3(ac, ap);
@@ -279,12 +283,30 @@ LF_HD F3 nearest_on_triangle(F3 p, F3 a, F3 b, F3 c) {
   else if (on_bc) { num = e43; den = e43 + e56; }
   else { num = 1.0f; den = (va + vb) + vc; }
   float q;
-  if (kPlain && num > 0x1p-100f && den > 0x1p-100f && den < 0x1p100f) q = quotient(num, divisor(den));
-  else q = num / den;
+  // (on an edge num <= den)
+  if (kPlain && num > 0x1p-48f && den > 0x1p-100f && den < 0x1p52f) q = quotient(num, divisor(den));
+  else {
+    q = num / den;
+    if (kPlain && !(fabsf(q) < INFINITY)) *odd = 1u;
+  }
   if (on_ab) return axpy3(a, q, ab);
   if (on_ac) return axpy3(a, q, ac);
   if (on_bc) return axpy3(b, q, sub3(c, b));
   return axpy3(axpy3(a, vb * q, ab), vc * q, ac);
+}
+
+// Whether quotient() and root() may take the view loop of a triangle that some
+// view sees, whose depths are zlo and more and whose coordinates and the rig's
+// eyes are at most `far`: their operands and results then lie where those are
+// exact, unless a nearest point is odd.  For every active view |delta| >= |P0 - e| / 256 >= zlo / 256, at most
+// 3 far; the nearest point is no farther from the eye than P0, its depth at least
+// zlo / 2 (rounding moves it by far / 2^20 at most), so the vectors v and w are
+// at most 2^9 and at least zlo / 4 far long; and depth^3 / (fx fy |delta|) is at
+// least zlo^3 / (24 fx fy far).  (Components of the normal below 2^-100 give
+// quotients too small to change v or w.)
+LF_HD bool plain_operands(const Rig& rg, float zlo, float far) {
+  return zlo >= 0x1p-30f && far < 0x1p30f && rg.fx >= 1.0f && rg.fx < 0x1p30f && rg.fy >= 1.0f && rg.fy < 0x1p30f &&
+         zlo > far * 0x1p-18f && zlo * zlo * zlo > rg.fxfy * far * 0x1p-94f;
 }
 
 // ---------------------------------------------------------------- lattice

@@ -159,7 +159,8 @@ struct ViewSums {
   float lx, ly, A, ad_lo, ad_hi_neg;
 };
 template <bool kPlain>
-__device__ __forceinline__ ViewSums sum_views(const Rig& rg, const TriRec& R, F3 P0, F3 P1, F3 P2, int first, int step) {
+__device__ __forceinline__ ViewSums sum_views(const Rig& rg, const TriRec& R, F3 P0, F3 P1, F3 P2, int first, int step,
+                                              uint32_t* odd) {
   ViewSums S{0, INFINITY, INFINITY, INFINITY, INFINITY, 0.0f};
   const float p0y2 = P0.y * P0.y, p0z2 = P0.z * P0.z;
   // x * 256 < -0.5 rounds below 0; x * 256 > 256 W + 0.5 rounds above 256 W
@@ -178,7 +179,7 @@ __device__ __forceinline__ ViewSums sum_views(const Rig& rg, const TriRec& R, F3
     if (fmaxf(x0, fmaxf(x1, x2)) < x_left || fminf(x0, fminf(x1, x2)) > x_right) continue;
     ++S.nact;
     const F3 e{b, 0.0f, 0.0f};
-    const F3 Ps = nearest_on_triangle<kPlain>(e, P0, P1, P2);
+    const F3 Ps = nearest_on_triangle<kPlain>(e, P0, P1, P2, odd);
     const F3 d = sub3(Ps, e);
     const float ad = fabsf(delta), Zs = Ps.z;
     const Divisor dd = divisor(delta);
@@ -221,6 +222,7 @@ __global__ void __launch_bounds__(256) k_tri_setup(SetupArgs a) {
   __shared__ uint32_t l_rows[kTris];  // its rows, then the rows before this triangle's
   __shared__ uint32_t l_cnt[kTris];
   __shared__ int32_t l_jlo[kTris], l_jhi[kTris];
+  __shared__ uint32_t l_odd[256];     // a lane's view loop met a nearest point off its triangle
   __shared__ uint64_t ws4[4];
   const int tl = threadIdx.x / kVL, sub = threadIdx.x % kVL;
   const int64_t t = (int64_t)blockIdx.x * kTris + tl;
@@ -265,17 +267,19 @@ __global__ void __launch_bounds__(256) k_tri_setup(SetupArgs a) {
     }
     // triangles that no view can see skip the view loop (see may_be_seen)
     const bool seen = ok && may_be_seen(rg, R);
-    // Operands of the view loop in the middle of the binary32 range: depths from
-    // z_near up, coordinates and focal lengths moderate (so that no projected
-    // pixel edge degenerates), the plane distance at least z_near / 256.
-    float pmax = 0.0f;
+    // the wave's view loops in the middle of the binary32 range, or with the plain operators
+    float far = fmaxf(fabsf(rg.eye_lo), fabsf(rg.eye_hi));
     for (int k = 0; k < 3; ++k)
-      for (int q = 0; q < 3; ++q) pmax = fmaxf(pmax, fabsf(P[k][q]));
-    const bool plain = rg.znear >= 0x1p-30f && rg.fx >= 1.0f && rg.fx < 0x1p30f && rg.fy >= 1.0f && rg.fy < 0x1p30f &&
-                       fmaxf(fabsf(rg.eye_lo), fabsf(rg.eye_hi)) < 0x1p30f &&
-                       __builtin_amdgcn_ballot_w64(seen && !(pmax < 0x1p30f)) == 0;
+      for (int q = 0; q < 3; ++q) far = fmaxf(far, fabsf(P[k][q]));
+    const float zlo = fminf(P[0][2], fminf(P[1][2], P[2][2]));
+    const bool plain = __builtin_amdgcn_ballot_w64(seen && !plain_operands(rg, zlo, far)) == 0;
     ViewSums S{0, INFINITY, INFINITY, INFINITY, INFINITY, 0.0f};
-    if (seen) S = plain ? sum_views<true>(rg, R, P0, P1, P2, sub, kVL) : sum_views<false>(rg, R, P0, P1, P2, sub, kVL);
+    uint32_t* const odd = &l_odd[threadIdx.x];  // in LDS: the loop has no register for it to merge at each view
+    *odd = 0u;
+    if (plain && seen) S = sum_views<true>(rg, R, P0, P1, P2, sub, kVL, odd);
+    if (!plain || __builtin_amdgcn_ballot_w64(*odd != 0u)) {
+      if (seen) S = sum_views<false>(rg, R, P0, P1, P2, sub, kVL, odd);
+    }
     nact = group_sum<kVL>(S.nact);
     const float lxmin = group_min<kVL>(S.lx), lymin = group_min<kVL>(S.ly), Amin = group_min<kVL>(S.A);
     const float admin = group_min<kVL>(S.ad_lo), admax = 0.0f - group_min<kVL>(S.ad_hi_neg);
