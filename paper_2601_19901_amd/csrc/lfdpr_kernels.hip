@@ -922,8 +922,19 @@ __device__ __forceinline__ void wave_sync_lds() {
 // covered pixel went through the passes by itself, 1294 with held entries; 192
 // views of 640 x 480 5280, 8069 and 3809.  Where the LDS has room its queue is
 // 2 to 4 % faster (48 views of 512 x 512: 1183 against 1208 us).
+//
+// Shaded tiles (no queue of owned pixels there): where coarse textures make
+// points of many pixels, shading each owned pixel is dearer than shading each
+// point.  A view in which the wave's large boxes (beyond kLaneSteps steps) hold
+// kAheadPixels or more is shaded ahead, each lane its own point, and its pixels
+// take the lane's colour; entries of views with and without such colours do not
+// wait together.  48 views of 600 x 512, textures of 16 texels: 687 us with a
+// lane's colour for all of its pixels, 836 shading each pixel, 660 so; of 8
+// texels 1714, 1570 and 1191.  (From 96, 128 or 384 box pixels on: within 2 %;
+// from 768: 3 to 15 % slower.)  The test costs 2 % where textures are fine.
 constexpr int kSplatQueue = 191;        // entries: 63 waiting and 128 new ones at most
 constexpr int32_t kLaneSteps = 8;       // steps of two pixels that a lane walks alone
+constexpr int kAheadPixels = 192;       // box pixels of a wave in a view from which its points are shaded ahead
 constexpr int kOwnQueue = 128;          // 63 waiting and 64 new ones
 constexpr float kRound = 12582912.0f;    // 1.5 * 2^23: adding it rounds to an integer (ties to even) ...
 constexpr int32_t kRoundBits = 0x4B400000;  // ... held in the sum's bits, offset by this
@@ -1080,13 +1091,26 @@ __device__ __forceinline__ void splat_wave(const Item& item, bool valid, uint64_
   const bool rowmajor = item.key_layout != 0;
   uint32_t qn = 0, on_n = 0;  // waiting entries: covered pixels; owned pixels (kPBR)
   uint32_t held = 0;          // kHeld: lane k's waiting entry, k < qn
+  constexpr bool kAhead = kPBR && kQuilt;
+  uint32_t ahead = 0;         // kAhead: 1 if this view's colours are in col_l, lane k's of point k
+  uint32_t col_l = 0;
   float eye_l = 0.0f, ks_l = 0.0f;  // eye offset and lens shift of view g0 + lane
   int g0 = r_begin;
 
-  // Colour (Eqs. 8-9; kPBR: shaded) of owned pixel e at depth Z, and its key.
-  auto emit_key = [&](uint32_t e, float Z, bool on, float b, float nx, float delta) {
+  // Colour (Eqs. 8-9; kPBR: shaded) of owned pixel e at depth Z, and its key.  kAhead: the view's colours may be there
+  // already; `first` puts them there, for entries of no pixel.
+  auto emit_key = [&](uint32_t e, float Z, bool on, float b, float nx, float delta, bool first, bool there) {
     const int src = (int)((e & 63u) << 2);
     const uint32_t x = (e >> 6) & xm, y = (e >> ysh) & ym, rr = e >> rsh;
+    auto tile_key = [&](uint32_t col) {
+      lds_key_min(qt->keys + (((g0 - qt->r_lo + (int)rr) * qt->rows + ((int)y - qt->y_lo)) * rg.W + (int)x),
+                  ((uint64_t)__float_as_uint(Z) << 32) | col);
+    };
+    if (kAhead && there) {
+      const uint32_t col = from_lane(src, col_l);
+      if (on) tile_key(col);
+      return;
+    }
     const float ac = from_lane(src, acell), ruv = from_lane(src, T.ruv);
     const float smin = from_lane(src, T.smin), smax = from_lane(src, T.smax), irange = from_lane(src, T.irange);
     const uint32_t lo = from_lane(src, pt.tvmin), hi = from_lane(src, pt.tvmax);
@@ -1127,7 +1151,8 @@ __device__ __forceinline__ void splat_wave(const Item& item, bool valid, uint64_
     }
     const uint64_t key = ((uint64_t)__float_as_uint(Z) << 32) | col;
     if constexpr (kQuilt) {
-      lds_key_min(qt->keys + (((g0 - qt->r_lo + (int)rr) * qt->rows + ((int)y - qt->y_lo)) * rg.W + (int)x), key);
+      if (kAhead && first) col_l = col;
+      else tile_key(col);
     } else {
       const uint32_t r = (uint32_t)g0 + rr;
       const uint32_t row = rowmajor ? y * (uint32_t)rg.n_views + r : r * (uint32_t)rg.H + y;
@@ -1137,11 +1162,11 @@ __device__ __forceinline__ void splat_wave(const Item& item, bool valid, uint64_
 
   auto emit_queued = [&](uint2 q, bool on) {
     const float b = from_lane((int)((q.x >> rsh) << 2), eye_l), nx = from_lane((int)((q.x & 63u) << 2), T.nx);
-    emit_key(q.x, __uint_as_float(q.y), on, b, nx, from_lane((int)((q.x & 63u) << 2), T.h) - nx * b);
+    emit_key(q.x, __uint_as_float(q.y), on, b, nx, from_lane((int)((q.x & 63u) << 2), T.h) - nx * b, false, false);
   };
 
   // Covered pixel e of each lane of mask `on`: ray hit, depth, ownership.
-  auto take = [&](uint32_t e, uint64_t on) {
+  auto take = [&](uint32_t e, uint64_t on, bool there) {
     const int src = (int)((e & 63u) << 2);
     const uint32_t x = (e >> 6) & xm, y = (e >> ysh) & ym;
     const int vsrc = (int)((e >> rsh) << 2);
@@ -1178,7 +1203,7 @@ __device__ __forceinline__ void splat_wave(const Item& item, bool valid, uint64_
         emit_queued(q, true);
       }
     } else {
-      emit_key(e, Z, own, b, nx, delta);
+      emit_key(e, Z, own, b, nx, delta, false, there);
     }
   };
 
@@ -1191,7 +1216,8 @@ __device__ __forceinline__ void splat_wave(const Item& item, bool valid, uint64_
     held = (uint32_t)lane >= qn ? got : held;
     qn = (uint32_t)__builtin_amdgcn_readfirstlane((int)(qn + n));
     if (qn >= 64) {
-      take(held, ~0ull);
+      if (kAhead && ahead) take(held, ~0ull, true);
+      else take(held, ~0ull, false);
       held = got;
       qn -= 64;
     }
@@ -1215,12 +1241,14 @@ __device__ __forceinline__ void splat_wave(const Item& item, bool valid, uint64_
       wave_sync_lds();
       const uint32_t te = queue[qn + lane];
       wave_sync_lds();
-      take(te, ~0ull);
+      if (kAhead && ahead) take(te, ~0ull, true);
+      else take(te, ~0ull, false);
     }
   };
 
-  for (; g0 < r_end; g0 += group) {
+  for (int next; g0 < r_end; g0 = kAhead ? next : g0 + group) {
     const int g1 = min(r_end, g0 + group);
+    next = g1;
     const int rl = min(g0 + lane, r_end - 1);
     eye_l = rg.eye[rl];
     ks_l = rg.kshift[rl];
@@ -1283,9 +1311,24 @@ __device__ __forceinline__ void splat_wave(const Item& item, bool valid, uint64_
       // limit follows how many boxes exceed it.
       const int32_t steps = __mul24((w + 1) >> 1, nrows);
       uint64_t over = act & __builtin_amdgcn_ballot_w64(steps > kLaneSteps);
+      uint32_t many = 0;
       if (over) {
         const uint64_t over4 = over & __builtin_amdgcn_ballot_w64(steps > 4 * kLaneSteps);
+        if constexpr (kAhead) {
+          const int32_t px = 2 * kLaneSteps * (int32_t)(__builtin_popcountll(over) + 3 * __builtin_popcountll(over4));
+          if (px >= kAheadPixels || (over4 & __builtin_amdgcn_ballot_w64(steps > kAheadPixels / 2))) many = 1;
+        }
         if (__builtin_popcountll(over) - __builtin_popcountll(over4) > 3 * kLaneSteps / 4) over = over4;
+      }
+      if constexpr (kAhead) {
+        if (qn && (many | ahead)) {  // what waits has the colours of its own views: this one begins the next group
+          next = r;
+          break;
+        }
+        ahead = (uint32_t)__builtin_amdgcn_readfirstlane((int)many);
+        if (ahead)
+          emit_key((uint32_t)lane | ((uint32_t)(r - g0) << rsh), 0.0f, __builtin_amdgcn_inverse_ballot_w64(act), b, T.nx,
+                   T.h - T.nx * b, true, false);
       }
       uint64_t heavy = (act & wide) | over;
       const uint32_t e0 = (uint32_t)((bx0 << 6) + (int32_t)((uint32_t)lane | ((uint32_t)by0 << ysh))) + ((uint32_t)(r - g0) << rsh);
@@ -1360,7 +1403,8 @@ __device__ __forceinline__ void splat_wave(const Item& item, bool valid, uint64_
       wave_sync_lds();
       const uint64_t on = ~(~0ull << qn);
       qn = 0;
-      take(te, on);
+      if (kAhead && ahead) take(te, on, true);
+      else take(te, on, false);
     }
     if (kPBR && on_n) {
       wave_sync_lds();
