@@ -215,7 +215,7 @@ LF_HD bool may_be_seen(const Rig& rg, const TriRec& R) {
 // quotient in 2^-100 .. 2^100, x zero or in 2^-90 .. 2^90): the reciprocal and
 // two corrections by the fused residual (Markstein, IBM J. Res. Dev. 34, 1990)
 // and, for the root, the choice among three neighbours by the sign of their
-// products' residuals (Tuckerman's rounding test, in the same paper), which is
+// products' residuals (Tuckerman's rounding test), which is
 // what `/` and sqrtf come to there without their scaling and special cases.  A
 // divisor's reciprocal is shared by all of its quotients.  Host: the plain
 // operators.

@@ -7,12 +7,13 @@
 
 namespace lfdpr {
 
+// STAT_WRITTEN and STAT_COVERED are filled on the host, from their lines.
 enum StatSlot { STAT_ACTIVE = 0, STAT_OVERFLOW = 1, STAT_POINT_VIEWS = 2, STAT_TOTAL = 3, STAT_BIG = 4,
                 STAT_WRITTEN = 5, STAT_EMITTING = 6, STAT_COVERED = 7, STAT_TICKET = 8, STAT_SLOTS = 9 };
 
 // The statistics buffer continues with 64 lines of 128 bytes, cleared with it at
 // the start of a frame: the counter of a work queue of the point splat, and
-// shares of STAT_WRITTEN and STAT_COVERED.  (One address takes some 60 to 150
+// shares of the written and covered pixels.  (One address takes some 60 to 150
 // atomics in a microsecond: thousands of waves adding to one counter are a
 // launch's length by themselves.)
 constexpr int kWorkQueues = 64;
@@ -73,8 +74,7 @@ struct EmitArgs {
   const uint32_t* big;       // triangles emitted cooperatively, queued by the set-up
   const uint64_t* n_big;
   const uint32_t* counts;
-  const uint64_t* tile_base;  // exclusive point offset of each set-up workgroup's triangles
-  int32_t tile_step;          // entries of tile_base per emission tile (256 triangles)
+  const uint64_t* tile_base;  // exclusive point offset of each set-up workgroup's triangles: an emission tile
   uint64_t* offsets;          // written: first point of each triangle
   const TriEmit* em;
   Point* points;
@@ -105,8 +105,8 @@ struct SplatArgs {
   const TriMat* tm;          // physically based mode; else null
   const uint4* pmat;
   Shading sh;
-  uint64_t* stats;           // STAT_WRITTEN: pixels written (64-bit key updates issued);
-                             // STAT_COVERED: covered pixels visited (triangle-view order)
+  uint64_t* stats;           // the lines' LINE_WRITTEN: pixels written (64-bit key updates issued);
+                             // LINE_COVERED: covered pixels visited (triangle-view order)
   // triangle-major splat (used when pbox is not null)
   const TriEmit* em;
   const uint64_t* offsets;   // first point of each triangle

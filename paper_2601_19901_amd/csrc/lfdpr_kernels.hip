@@ -73,7 +73,7 @@ __global__ void __launch_bounds__(64) k_export_stats(const uint64_t* __restrict_
     out[1] = (int64_t)st[STAT_ACTIVE];
     out[2] = (int64_t)st[STAT_POINT_VIEWS];
     out[3] = (int64_t)st[STAT_OVERFLOW];
-    out[4] = (int64_t)(st[STAT_WRITTEN] + written);
+    out[4] = (int64_t)written;
     out[5] = cap;
   }
 }
@@ -496,8 +496,7 @@ __global__ void __launch_bounds__(256) k_tri_setup(SetupArgs a) {
 // The point offsets are an exclusive prefix sum of the per-triangle counts: each
 // set-up workgroup writes the sum of its triangles, k_scan_top turns the sums
 // into bases (one workgroup; also the grand total), and the emission kernel
-// adds the prefix within its tile of 256 triangles (one or eight workgroups of
-// the set-up).  Up to kScanTiles set-up workgroups, one sum per thread, the last
+// adds the prefix within its tile, the triangles of one set-up workgroup.  Up to kScanTiles set-up workgroups, one sum per thread, the last
 // of them to finish does it instead of a launch (a frame of 1,280 triangles 53.1
 // -> 51.4 us).
 __global__ void __launch_bounds__(1024) k_scan_top(uint64_t* __restrict__ tile_sum,
@@ -564,12 +563,11 @@ __device__ __forceinline__ void write_head(Point* pts, uint64_t gi, uint32_t t, 
 // Emission, one launch: workgroups [0, kEmitBigBlocks) take the queued
 // triangles with more than kBigCells cells, one triangle per workgroup at a
 // time (lanes take rows, a block scan places them); the others take tiles of
-// 256 triangles: each lane writes its triangle's point offset (tile base +
+// kTile triangles (256, 32 in small scenes, as a workgroup of the set-up): each lane writes its triangle's point offset (tile base +
 // prefix within the tile), then the rows of the tile's small triangles are
 // spread over the lanes; rows follow each other in emission order, so a scan of
 // their cells places them.  Against a lane per triangle (up to 96 cells in one
 // lane): 1.0M triangles 95 -> 77 us, 0.18M 62 -> 34 us.
-constexpr int kEmitTile = 256;  // triangles per workgroup of a large scene
 constexpr unsigned kEmitBigBlocks = 1024;
 
 template <int kTile>
@@ -586,7 +584,7 @@ __device__ __forceinline__ void emit_big(const EmitArgs& a, uint64_t* ws4) {
     uint64_t wsum = wave_sum(cu);
     if (lane == 0) ws4[wv] = wsum;
     __syncthreads();
-    const uint64_t base = a.tile_base[t0 / kTile * a.tile_step] + (ws4[0] + ws4[1]) + (ws4[2] + ws4[3]);
+    const uint64_t base = a.tile_base[t0 / kTile] + (ws4[0] + ws4[1]) + (ws4[2] + ws4[3]);
     __syncthreads();
     Lattice L;
     lattice_init(L, E.s1, E.t1, E.s2, E.t2);
@@ -637,8 +635,8 @@ __global__ void __launch_bounds__(256) k_emit(EmitArgs a) {
   const int64_t t0 = tile * kTile, t = t0 + threadIdx.x;
   const bool mine = (kTile == 256 || threadIdx.x < kTile) && t < a.nt;
   const uint32_t cnt = mine ? a.counts[t] : 0u;
-  const uint64_t tbase = a.tile_base[tile * a.tile_step];
-  const uint32_t first = (uint32_t)block_excl_scan(cnt, ws4);  // 256 triangles of at most kCellCap points
+  const uint64_t tbase = a.tile_base[tile];
+  const uint32_t first = (uint32_t)block_excl_scan(cnt, ws4);  // kTile triangles of at most kCellCap points
   if (mine) a.offsets[t] = tbase + first;
   if (a.tris) {
     const uint64_t slot = wave_append(cnt > 0, a.n_tris);
@@ -722,7 +720,7 @@ __device__ __forceinline__ void splat_corners(const Rig& rg, const TriRec& T, in
   }
 }
 
-// Rows that splat_point can write for a point in any view: the triangle's rows
+// Rows that splat_wave can write for a point in any view: the triangle's rows
 // (guard band, the whole triangle above or below the view) met with the splat
 // rectangle's rows `rows` (PointBox).  False when none.
 __device__ __forceinline__ bool quilt_point_rows(int32_t H, const TriRec& T, int32_t rows, int32_t& r0, int32_t& r1) {
@@ -862,10 +860,6 @@ struct QuiltTile {
 __device__ __forceinline__ float table_f32(const float* p, int i) {
   typedef const __attribute__((address_space(4))) float const_f32;
   return ((const_f32*)p)[i];
-}
-
-__device__ __forceinline__ float uniform_f32(float x) {
-  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
 }
 
 // Orders this wave's LDS accesses around it (its lanes exchange data there).
@@ -2053,8 +2047,8 @@ __device__ __forceinline__ void store_panel(const InterleaveArgs& a, int64_t Y, 
 
 // One lane per four consecutive panel pixels.  Panel rows are spread over the
 // XCDs in contiguous bands so that each view row is fetched into one L2.
-// View stacks of less than 4 GiB whose planes are below 16 MiB (kInterleaveSmall
-// below): a tap's byte is loaded from a 32-bit offset, view * plane + (row +
+// View stacks of less than 4 GiB whose planes are below 16 MiB (the rule is
+// launch_interleave's): a tap's byte is loaded from a 32-bit offset, view * plane + (row +
 // column) with the row the same for the whole workgroup and the column for a
 // pixel's three channels, so a tap costs five vector instructions instead of
 // some 25 of 64-bit address arithmetic, which bounded the eight-tap modes
@@ -2271,15 +2265,13 @@ void launch_scan(uint64_t* tile_sum, const uint64_t* tile_stat, int64_t nt, uint
   k_scan_top<<<1, 1024, 0, s>>>(tile_sum, tile_stat, (nt + per - 1) / per, stats);
 }
 
-void launch_emit(const EmitArgs& args, int fetch_blocks, hipStream_t s) {
-  if (args.nt <= 0) return;
-  EmitArgs a = args;
-  // tiles of 32 triangles spread the rows of a small scene over more workgroups
-  const int tile = a.nt < kSplitTris ? 32 : kEmitTile;
-  a.tile_step = tile * setup_lanes(a.nt) / 256;
+void launch_emit(const EmitArgs& a, int fetch_blocks, hipStream_t s) {
+  if (a.nt <= 0) return;
+  // the set-up's tiles: 32 triangles spread the rows of a small scene over more workgroups
+  const int tile = 256 / setup_lanes(a.nt);
   const unsigned g = kEmitBigBlocks + nblk(a.nt, tile);
   if (tile == 32) k_emit<32><<<g, 256, 0, s>>>(a);
-  else k_emit<kEmitTile><<<g, 256, 0, s>>>(a);
+  else k_emit<256><<<g, 256, 0, s>>>(a);
   if (a.pbox && a.tm)
     k_fetch<true, true><<<fetch_blocks, 256, 0, s>>>(a);
   else if (a.pbox)

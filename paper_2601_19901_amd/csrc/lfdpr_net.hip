@@ -197,7 +197,7 @@ __global__ void __launch_bounds__(kConvThreads, 4) k_conv3x3(const uint16_t* __r
     x0 = (pos % tiles_x) * kTX;
   };
   // Staging items of this thread, the same for every tile.  Layers 2-4: item j
-  // is 16-byte group threadIdx % 4 of LDS pixel q = threadIdx / 4 + 64 j, at
+  // is 16-byte group threadIdx % 4 of LDS pixel q = threadIdx / 4 + kConvThreads / 4 j, at
   // tile row q / TW and column q % TW (rows from kTY + 2 on lie past the staged
   // tile).  Layer 1 (GATHER) stages plane by plane -- views v-2 .. v+2 of the
   // compact input, then the blur, 8 bytes per pixel -- in pairs of pixels from
@@ -307,7 +307,7 @@ __global__ void __launch_bounds__(kConvThreads, 4) k_conv3x3(const uint16_t* __r
     // the epilogue's side input (residual or ReLU mask), clamped into the image
     // and used only where in range: the residual is requested before the MFMAs;
     // the mask (two 32-channel tiles) after them, which keeps the backward
-    // instantiation at three waves per SIMD
+    // instantiation within 128 registers (four waves per SIMD)
     Chans side[4];
     auto load_side = [&]() {
 #pragma unroll

@@ -13,7 +13,9 @@ from test_gpu_net import assert_bf16_close, bits_to_f, f_to_bits, get16, make_ne
 pytestmark = pytest.mark.gpu
 
 V, H, W = 48, 75, 200
-CHECKED = (0, 11, 25, 26, 38, 39, 47)  # 40 tiles a view: tiles 1,024 and 1,536 are in views 25 and 38
+# Each XCD's 64 workgroups take an eighth of the order, six views of 40 tiles: the first, second, third and fourth tile
+# of a workgroup lie in the views at places 0-1, 1-3, 3-4 and 4-5 of an eighth.
+CHECKED = (0, 11, 25, 26, 38, 39, 47)
 
 
 def test_three_and_four_tiles_per_workgroup():
