@@ -873,7 +873,8 @@ __device__ __forceinline__ void wave_sync_lds() {
 // item's rig; `item` and the view range are wave-uniform, every lane of the
 // wave calls, and lanes with `valid` false take part without a point.
 //
-// What bounds it: vector issue.  A (point, view) pair's splat box holds 1.7
+// What bounds it: vector issue (the SIMDs issue vector instructions in 97 % of
+// its cycles, in the quilt's tiles in all).  A (point, view) pair's splat box holds 1.7
 // pixels on average but up to 4.4 in the slowest lane of 64, and of the box
 // pixels 54 % lie inside the triangle and 29 % belong to the point, so a lane
 // that carries its own pixels through the ray, the division, the ownership
@@ -890,7 +891,7 @@ __device__ __forceinline__ void wave_sync_lds() {
 // triangle took 1.5 ms): all lanes walk it, 64 pixels at a time.
 // Measured on a million-triangle frame (3.0M points, 48 views of 512 x 512)
 // against one lane carrying each pixel to its key: 8.3e8 -> 4.8e8 vector
-// instructions, 2.48 -> 1.17 ms (0.93 with the work items of k_splat and the
+// instructions, 2.48 -> 1.17 ms (0.97 with the work items of k_splat and the
 // statistics' lines).
 // A queue entry is one word: lane (6 bits), x, y, and the view within a group
 // of as many views as the remaining bits number (64 at most; 4 at 4096 x 4096).
